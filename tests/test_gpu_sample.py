@@ -214,3 +214,23 @@ def test_free_energy_parity_ea3d(prec):
         dF = abs(stats[0] - mean_ref)
         say(f"prec {prec} beta {beta}: |dF_q/N| = {dF:.3e}")
         assert dF <= 1e-4
+
+
+@pytest.mark.parametrize("n,batch,offset", [(1, 3, 0), (191, 33, 0), (192, 16, 0), (383, 17, 1), (384, 4096, 0),
+                                            (385, 4097, 0), (400, 4095, 1), (1040, 4100, 0), (4096, 33, 0)])
+def test_energy_dense_tile_edges(n, batch, offset):
+    """Dense energies at the edges of the kernel's row blocks and sample tiles, with rows and matrices that
+    are not 16-byte aligned (offset: J starts that many floats into its allocation), against FP64.  Bound: each
+    F_i = sum_j J_ij s_j is a sum of n FP32 terms, within n 2^-24 sum_j |J_ij|; the rest is FP64, rounded once."""
+    rng = np.random.default_rng(n)
+    J = rng.standard_normal((n, n)).astype(np.float32)
+    store = torch.zeros(n * n + offset, device="cuda")
+    store[offset:] = torch.as_tensor(J.reshape(-1), device="cuda")
+    c = fv.CouplingsC(n_spins=n, kind=fv.BONDS_DENSE, degree=0, nbr=None, J=store.data_ptr() + 4 * offset)
+    coup = fv.Couplings(n, fv.BONDS_DENSE, 0, None, store, c)
+    s = random_spins(batch, n, 3)
+    E = to_np(fv.energy(coup, torch.as_tensor(s, device="cuda"))).astype(np.float64)
+    x = s.astype(np.float64)
+    ref = -0.5 * ((x @ J.astype(np.float64).T) * x).sum(1)
+    tol = 0.5 * np.abs(J.astype(np.float64)).sum() * n * 2.0 ** -24 + np.abs(ref) * 2.0 ** -24
+    assert np.all(np.abs(E - ref) <= tol)
