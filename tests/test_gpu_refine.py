@@ -114,3 +114,35 @@ def test_train_step_distill_equals_composed_calls(prec):
     torch.cuda.synchronize()
     assert stats[0] == st[0] and stats[1] == st[1]
     assert np.array_equal(to_np(m1.params), to_np(m2.params))
+
+
+@pytest.mark.parametrize("n,degree,batch", [(1, 1, 3), (5, 2, 9), (16, 4, 130), (37, 8, 70), (130, 6, 5), (1021, 6, 3),
+                                            (1030, 4, 3), (4096, 5, 2), (4097, 3, 2), (50, 9, 6)])
+def test_lmc_any_graph_and_colouring(n, degree, batch):
+    """Refinement over random neighbour tables with empty slots and arbitrary colours (not a checkerboard, some
+    sites never updated), at the edges of the per-configuration thread groups and of both kernels' ranges."""
+    rng = np.random.default_rng(n + degree)
+    nbr = rng.integers(0, n, (n, degree)).astype(np.int32)
+    nbr[rng.random((n, degree)) < 0.2] = -1
+    J = rng.standard_normal((n, degree)).astype(np.float32)
+    col = rng.choice(np.array([0, 0, 1, 1, 2], np.int8), n)
+    spins = random_spins(batch, n, 4)
+    tn, tj, tc = (torch.as_tensor(a, device="cuda") for a in (nbr, J, col))
+    sweeps, beta, seed, tag = 3, 0.7, (3 << 32) | 5, 17
+    g = fv.LmcGraph(n, tn, tj, tc, fv.LmcC(degree=degree, nbr=tn.data_ptr(), J=tj.data_ptr(), colour=tc.data_ptr(),
+                                           sweeps=sweeps))
+    t = torch.as_tensor(spins, device="cuda")
+    acc = torch.full((batch,), -1, dtype=torch.int32, device="cuda")
+    fv.lmc_refine(g, t, beta, seed, tag, acc)
+    torch.cuda.synchronize()
+    got, gacc = to_np(t), to_np(acc)
+    adj = [[(int(j), float(w)) for j, w in zip(nbr[i], J[i]) if j >= 0] for i in range(n)]
+    excused = 0
+    for b in range(batch):
+        ref, racc, marg = refine.metropolis_checkerboard(spins[b:b + 1], adj, col, beta, sweeps, seed, tag, b0=b,
+                                                         margins=True)
+        if marg[0] < TIE:
+            excused += 1
+            continue
+        assert np.array_equal(got[b], ref[0]) and gacc[b] == racc[0], f"configuration {b}"
+    assert excused <= max(1, batch // 8)
