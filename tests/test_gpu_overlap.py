@@ -44,3 +44,24 @@ def test_overlap_histogram_moments_at_benchmark_size():
     G = f.T @ f                                            # exact: integer entries <= B
     m2 = (int(np.rint((G * G).sum())) - B * N * N) // 2    # sum over a < b of (s_a . s_b)^2
     assert int((got * x * x).sum()) == m2
+
+
+@pytest.mark.parametrize("B,N,start", [(64, 64, 0), (63, 1, 3), (3968, 65, 0), (3969, 63, 1), (4033, 130, 5),
+                                       (7937, 70, 0), (8065, 1023, 2), (8000, 1024, 0), (300, 9000, 0)])
+def test_overlap_histogram_block_edges(B, N, start):
+    """Exact counts at the edges of the three block sizes and of the histogram copies, with ragged rows and a
+    batch that starts `start` bytes into its allocation.  The counts are those of the integer product S S^T."""
+    rng = np.random.default_rng(B + N)
+    s = np.where(rng.random((B, N)) < 0.3, -1, 1).astype(np.int8)
+    store = torch.zeros(B * N + start, dtype=torch.int8, device="cuda")
+    store[start:] = torch.as_tensor(s.reshape(-1), device="cuda")
+    say(f"overlap B={B} N={N} start={start}")
+    got = to_np(fv.overlap_histogram(store[start:].view(B, N)))
+    f = s.astype(np.float32)
+    ref = np.zeros(N + 1, dtype=np.int64)
+    for a in range(0, B, 1024):                    # integers below 2^24: exact in float32
+        q = f[a:a + 1024] @ f.T
+        k = ((q + N) / 2).astype(np.int64)
+        upper = np.arange(B)[None, :] > np.arange(a, min(a + 1024, B))[:, None]
+        ref += np.bincount(k[upper], minlength=N + 1)
+    assert np.array_equal(got, ref)
