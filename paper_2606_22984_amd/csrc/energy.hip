@@ -5,7 +5,8 @@
 // LDS with coalesced 16-byte loads, each thread sums its sites' stored pairs
 // (neighbour table and bonds are shared by all samples and stay in L2), then a
 // fixed-order block reduction.  +/-J bonds accumulate in int32: exact.
-// Dense (SK) bonds are a contraction of the spins with J, on FP32 MFMA (below).
+// Dense (SK) bonds: one workgroup per 16 samples so every J row read from L2
+// serves 16 samples (below).
 #include "device_common.h"
 #include "fvan_internal.h"
 
@@ -55,143 +56,162 @@ __global__ __launch_bounds__(kEThreads) void energy_ell_kernel(int n, int deg, c
   if (threadIdx.x == 0) out[b] = -tot;
 }
 
-// Dense (SK) bonds, E_b = -1/2 sum_i s_bi F_bi with F = S J^T on FP32 MFMA.
-// One workgroup (8 waves) owns 16 SBT samples, staged as int8 in LDS; wave w takes
-// blocks of 16 IT rows i of J and runs the whole contraction over j for them, so
-// every J element a lane loads feeds SBT products and every spin IT; the block's F
-// is multiplied by its spins in registers and summed in FP64, in a fixed order.
-// Bound: FP32 MFMA (2 B n^2 flop: 28 us at 8192 x 512 and 152 TFLOP/s).  The
-// vector-unit form (an integer product, a conversion and an FMA per (i, j, sample))
-// took 331 us there; this one takes 50 us, the waves waiting on L2 for the
-// next J fragments about half of the time.
-constexpr int kDenseThreads = 512;
-constexpr int kDenseWaves = kDenseThreads / 64;
+// Dense (SK) bonds.  One workgroup (4 waves) per kDenseS samples; wave w takes the
+// rows i = w, w + 4, ... of J, lane l the columns j = l, l + 64, ..., and every J
+// element a lane loads serves all the samples:
+//   acc += J_ij (s_i s_j), rows in order, then a fixed-order block sum.
+// energy_dense_general_kernel forms s_i s_j from LDS for every (i, j, sample).
+//
+// For +-1 spins acc is carried multiplied by s_i instead: s_i (acc + J_ij s_i s_j) =
+// s_i acc + J_ij s_j with the same roundings (a sign flip is exact), so a row costs
+// one FMA per element with the lane's s_j held in registers, and one sign flip per
+// row and sample.  That is the vector FMA rate (2 B n^2 flop at 78 TFLOP/s without
+// packed FP32: 55 us at 8192 x 512).  Measured there: 331 us with the product formed
+// per element, 77 us now.  (FP32 MFMA takes 50 us in another summation order, but
+// the weights of a training step then differ in the last bit, which the sampling of
+// the next step amplifies into other spins.)
+constexpr int kDenseS = 16;
 
-// J[i][k .. k + 4), zero outside the matrix; VEC: rows are 16-byte aligned
-template <bool VEC>
-__device__ __forceinline__ float4 load_j(const float* __restrict__ J, int n, int i, int k) {
-  if (i >= n || k >= n) return make_float4(0.f, 0.f, 0.f, 0.f);
-  const float* p = J + (size_t)i * n + k;
-  if constexpr (VEC) return *reinterpret_cast<const float4*>(p);
-  return make_float4(p[0], k + 1 < n ? p[1] : 0.f, k + 2 < n ? p[2] : 0.f, k + 3 < n ? p[3] : 0.f);
+__global__ __launch_bounds__(kEThreads) void energy_dense_general_kernel(int n, int batch, const float* __restrict__ J,
+                                                                         const int8_t* __restrict__ spins,
+                                                                         float* __restrict__ out) {
+  extern __shared__ int8_t sm[];    // [kDenseS][n]
+  __shared__ float red[kEThreads / 64];
+  const int b0 = blockIdx.x * kDenseS;
+  const int ns = min(kDenseS, batch - b0);
+  for (int i = threadIdx.x; i < kDenseS * n; i += kEThreads) {
+    const int s = i / n, j = i % n;
+    sm[i] = s < ns ? spins[(size_t)(b0 + s) * n + j] : (int8_t)0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float acc[kDenseS];
+#pragma unroll
+  for (int s = 0; s < kDenseS; ++s) acc[s] = 0.f;
+  for (int i = wave; i < n; i += kEThreads / 64) {
+    const float* Ji = J + (size_t)i * n;
+    for (int j = lane; j < n; j += 64) {
+      const float w = Ji[j];
+#pragma unroll
+      for (int s = 0; s < kDenseS; ++s) acc[s] += w * (float)(sm[s * n + i] * sm[s * n + j]);
+    }
+  }
+  for (int s = 0; s < kDenseS; ++s) {
+    const float tot = block_sum<float>(acc[s], red);
+    if (threadIdx.x == 0 && s < ns) out[b0 + s] = -0.5f * tot;
+    __syncthreads();
+  }
 }
 
-template <int SBT, int IT, bool VEC>
-__global__ __launch_bounds__(kDenseThreads) void energy_dense_kernel(int n, int batch, int stride,
-                                                                     const float* __restrict__ J,
-                                                                     const int8_t* __restrict__ spins,
-                                                                     float* __restrict__ out) {
-  constexpr int SB = 16 * SBT;
-  extern __shared__ __align__(16) int8_t sm[];        // [SB][stride], zero past n
-  __shared__ double red[kDenseWaves][SB];
-  const int b0 = blockIdx.x * SB;
-  const int ns = min(SB, batch - b0);
+// n <= 64 NJ, any spins (a workgroup that finds one that is not +-1 takes the
+// products as the general kernel does).
+template <int NJ>
+__global__ __launch_bounds__(kEThreads) void energy_dense_kernel(int n, int batch, const float* __restrict__ J,
+                                                                 const int8_t* __restrict__ spins,
+                                                                 float* __restrict__ out) {
+  constexpr int NP = 64 * NJ;                // columns, padded
+  __shared__ __align__(16) int8_t sm[kDenseS][NP];   // the tile's spins (absent samples 0, columns past n 1)
+  __shared__ uint32_t up[NP];                // bit s: sample s of the tile has spin +1 at site i
+  __shared__ float red[kEThreads / 64];
+  const int b0 = blockIdx.x * kDenseS;
+  const int ns = min(kDenseS, batch - b0);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c = lane & 15, g = lane >> 4;
-  if (((n | (int)((uintptr_t)spins & 15)) & 15) == 0) {
-    for (int i = threadIdx.x; i < SB * (n >> 4); i += kDenseThreads) {
-      const int s = i / (n >> 4), j = (i % (n >> 4)) * 16;
-      *reinterpret_cast<uint4*>(sm + s * stride + j) =
-          s < ns ? *reinterpret_cast<const uint4*>(spins + (size_t)(b0 + s) * n + j) : make_uint4(0u, 0u, 0u, 0u);
+  const int8_t* base = spins + (size_t)b0 * n;
+  if (n == NP && ((uintptr_t)base & 15) == 0) {
+    constexpr int V = kDenseS * NP / 16;     // 16-byte pieces of the tile, whole rows
+#pragma unroll
+    for (int x0 = 0; x0 < V; x0 += kEThreads) {
+      const int x = x0 + threadIdx.x;
+      if (x < V)
+        reinterpret_cast<uint4*>(&sm[0][0])[x] =
+            x < ns * (NP / 16) ? reinterpret_cast<const uint4*>(base)[x] : make_uint4(0u, 0u, 0u, 0u);
     }
   } else {
-    for (int i = threadIdx.x; i < SB * stride; i += kDenseThreads) {
-      const int s = i / stride, j = i % stride;
-      sm[i] = s < ns && j < n ? spins[(size_t)(b0 + s) * n + j] : (int8_t)0;
+#pragma unroll 8
+    for (int x = threadIdx.x; x < kDenseS * NP; x += kEThreads) {
+      const int s = x / NP, j = x % NP;
+      const int8_t v = base[min(s, ns - 1) * n + min(j, n - 1)];
+      sm[s][j] = j >= n ? (int8_t)1 : s < ns ? v : (int8_t)0;
     }
   }
   __syncthreads();
-  double e[SBT][4];
+  float sj[NJ][kDenseS];                     // the lane's spins
+  int odd = 0;                               // nonzero if one of them is not +-1
 #pragma unroll
-  for (int t = 0; t < SBT; ++t)
+  for (int q = 0; q < NJ; ++q)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) e[t][q] = 0.0;
-  for (int i0 = wave * 16 * IT; i0 < n; i0 += kDenseWaves * 16 * IT) {
-    floatx4 acc[SBT][IT];
+    for (int s = 0; s < kDenseS; ++s) {
+      const int v = sm[s][lane + 64 * q];
+      odd |= s < ns ? v * v - 1 : 0;
+      sj[q][s] = (float)v;
+    }
+  for (int i = threadIdx.x; i < NP; i += kEThreads) {
+    uint32_t m = 0;
 #pragma unroll
-    for (int t = 0; t < SBT; ++t)
+    for (int s = 0; s < kDenseS; ++s) m |= (sm[s][i] > 0 ? 1u : 0u) << s;
+    up[i] = m;
+  }
+  const bool all_pm1 = !__syncthreads_or(odd);
+  float acc[kDenseS];
 #pragma unroll
-      for (int u = 0; u < IT; ++u) acc[t][u] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float4 jv[IT];
+  for (int s = 0; s < kDenseS; ++s) acc[s] = 0.f;
+  if (all_pm1) {
+    uint32_t prev = 0xFFFFFFFFu;             // signs acc is carried with: +1 at first
+    float w[NJ];
+    auto load = [&](int i, float* v) {
 #pragma unroll
-    for (int u = 0; u < IT; ++u) jv[u] = load_j<VEC>(J, n, i0 + 16 * u + c, 4 * g);
-    for (int k = 0; k < n; k += 16) {
-      float4 jn[IT];                                  // the next chunk, in flight during this one's products
-#pragma unroll
-      for (int u = 0; u < IT; ++u) jn[u] = load_j<VEC>(J, n, i0 + 16 * u + c, k + 16 + 4 * g);
-      float a[SBT][4];
-#pragma unroll
-      for (int t = 0; t < SBT; ++t) {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(sm + (16 * t + c) * stride + k + 4 * g);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) a[t][q] = (float)(int8_t)(w >> (8 * q));
+      for (int q = 0; q < NJ; ++q) {
+        const int j = lane + 64 * q;
+        const float x = J[(size_t)min(i, n - 1) * n + min(j, n - 1)];   // no branch around the load
+        v[q] = j < n ? x : 0.f;
       }
+    };
+    load(wave, w);
+    for (int i = wave; i < n; i += kEThreads / 64) {
+      float nw[NJ];
+      load(i + kEThreads / 64, nw);          // the wave's next row, in flight during this one
+      const uint32_t cur = __builtin_amdgcn_readfirstlane(up[i]), flip = cur ^ prev;
+      prev = cur;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+      for (int s = 0; s < kDenseS; ++s)
+        acc[s] = __uint_as_float(__float_as_uint(acc[s]) ^ ((flip >> s & 1u) << 31));
 #pragma unroll
-        for (int u = 0; u < IT; ++u) {
-          const float jq = q == 0 ? jv[u].x : q == 1 ? jv[u].y : q == 2 ? jv[u].z : jv[u].w;
+      for (int q = 0; q < NJ; ++q)
 #pragma unroll
-          for (int t = 0; t < SBT; ++t)
-            acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][q], jq, acc[t][u], 0, 0, 0);
-        }
+        for (int s = 0; s < kDenseS; ++s) acc[s] += w[q] * sj[q][s];
 #pragma unroll
-      for (int u = 0; u < IT; ++u) jv[u] = jn[u];
+      for (int q = 0; q < NJ; ++q) w[q] = nw[q];
     }
-    // lane holds F of samples 16 t + 4 g + q at row i0 + 16 u + c
 #pragma unroll
-    for (int u = 0; u < IT; ++u) {
-      const int i = i0 + 16 * u + c;
+    for (int s = 0; s < kDenseS; ++s) acc[s] = prev >> s & 1u ? acc[s] : -acc[s];
+  } else {
+    for (int i = wave; i < n; i += kEThreads / 64)
 #pragma unroll
-      for (int t = 0; t < SBT; ++t)
+      for (int q = 0; q < NJ; ++q) {
+        const int j = lane + 64 * q;
+        if (j >= n) continue;
+        const float w = J[(size_t)i * n + j];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (i < n) e[t][q] += (double)(acc[t][u][q] * (float)sm[(16 * t + 4 * g + q) * stride + i]);
-    }
+        for (int s = 0; s < kDenseS; ++s)
+          acc[s] += w * (float)((int)sm[s][i] * (int)sm[s][j]);
+      }
   }
-#pragma unroll
-  for (int t = 0; t < SBT; ++t)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      double v = e[t][q];
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
-      if (c == 0) red[wave][16 * t + 4 * g + q] = v;
-    }
-  __syncthreads();
-  if ((int)threadIdx.x < ns) {
-    double tot = 0.0;
-    for (int w = 0; w < kDenseWaves; ++w) tot += red[w][threadIdx.x];
-    out[b0 + threadIdx.x] = (float)(-0.5 * tot);
+  for (int s = 0; s < kDenseS; ++s) {
+    const float tot = block_sum<float>(acc[s], red);
+    if (threadIdx.x == 0 && s < ns) out[b0 + s] = -0.5f * tot;
+    __syncthreads();
   }
-}
-
-template <int SBT, int IT>
-static void launch_dense_v(int n, int batch, int stride, const float* J, const int8_t* spins, float* out,
-                           hipStream_t s) {
-  const dim3 grid((batch + 16 * SBT - 1) / (16 * SBT));
-  const size_t lds = (size_t)16 * SBT * stride;
-  if (n % 4 == 0 && ((uintptr_t)J & 15) == 0)
-    hipLaunchKernelGGL((energy_dense_kernel<SBT, IT, true>), grid, dim3(kDenseThreads), lds, s, n, batch, stride, J,
-                       spins, out);
-  else
-    hipLaunchKernelGGL((energy_dense_kernel<SBT, IT, false>), grid, dim3(kDenseThreads), lds, s, n, batch, stride, J,
-                       spins, out);
 }
 
 static void launch_dense(int n, int batch, const float* J, const int8_t* spins, float* out, hipStream_t s) {
-  // rows of spins 16 bytes times an odd number apart: the 16 rows of an A fragment
-  // fall on different LDS banks (not at the largest n, where the padding would
-  // pass 64 KB)
-  int stride = (n + 15) / 16 * 16;
-  if (stride / 16 % 2 == 0 && 16 * (stride + 16) <= 65536) stride += 16;
-  // rows of J per wave: as many tiles as leave every wave a block; 32 samples per
-  // workgroup (each J fragment used twice) where that still gives every compute
-  // unit a workgroup and the rows fit 64 KB
-  if (n >= 384 && batch >= 4096 && 32 * stride <= 65536) launch_dense_v<2, 4>(n, batch, stride, J, spins, out, s);
-  else if (n >= 384) launch_dense_v<1, 4>(n, batch, stride, J, spins, out, s);
-  else if (n >= 192) launch_dense_v<1, 2>(n, batch, stride, J, spins, out, s);
-  else launch_dense_v<1, 1>(n, batch, stride, J, spins, out, s);
+  const dim3 grid((batch + kDenseS - 1) / kDenseS);
+  if (n > 512) {   // a lane's spins no longer fit its registers
+    hipLaunchKernelGGL(energy_dense_general_kernel, grid, dim3(kEThreads), kDenseS * n, s, n, batch, J, spins, out);
+    return;
+  }
+  auto kern = n <= 64 ? energy_dense_kernel<1> : n <= 128 ? energy_dense_kernel<2> : n <= 256 ? energy_dense_kernel<4>
+                                                                                     : energy_dense_kernel<8>;
+  hipLaunchKernelGGL(kern, grid, dim3(kEThreads), 0, s, n, batch, J, spins, out);
 }
 
 hipError_t launch_energy(const fvan_couplings& c, int32_t batch, const int8_t* spins, void* energy,

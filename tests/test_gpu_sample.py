@@ -216,12 +216,13 @@ def test_free_energy_parity_ea3d(prec):
         assert dF <= 1e-4
 
 
-@pytest.mark.parametrize("n,batch,offset", [(1, 3, 0), (191, 33, 0), (192, 16, 0), (383, 17, 1), (384, 4096, 0),
-                                            (385, 4097, 0), (400, 4095, 1), (1040, 4100, 0), (4096, 33, 0)])
+@pytest.mark.parametrize("n,batch,offset", [(1, 3, 0), (63, 33, 0), (64, 16, 0), (65, 17, 1), (128, 4096, 0),
+                                            (129, 4097, 0), (256, 4095, 1), (257, 100, 0), (512, 33, 0), (513, 20, 0),
+                                            (4096, 33, 0)])
 def test_energy_dense_tile_edges(n, batch, offset):
-    """Dense energies at the edges of the kernel's row blocks and sample tiles, with rows and matrices that
-    are not 16-byte aligned (offset: J starts that many floats into its allocation), against FP64.  Bound: each
-    F_i = sum_j J_ij s_j is a sum of n FP32 terms, within n 2^-24 sum_j |J_ij|; the rest is FP64, rounded once."""
+    """Dense energies at the edges of the kernel's column blocks and sample tiles, with rows and matrices that
+    are not 16-byte aligned (offset: J starts that many floats into its allocation), against FP64.  Bound: every
+    partial sum has at most n FP32 terms in a row, within n 2^-24 sum |J_ij| in all."""
     rng = np.random.default_rng(n)
     J = rng.standard_normal((n, n)).astype(np.float32)
     store = torch.zeros(n * n + offset, device="cuda")
@@ -234,3 +235,16 @@ def test_energy_dense_tile_edges(n, batch, offset):
     ref = -0.5 * ((x @ J.astype(np.float64).T) * x).sum(1)
     tol = 0.5 * np.abs(J.astype(np.float64)).sum() * n * 2.0 ** -24 + np.abs(ref) * 2.0 ** -24
     assert np.all(np.abs(E - ref) <= tol)
+
+
+def test_energy_dense_spins_other_than_pm1():
+    """Entries other than +-1 (here 0 and 2) keep the plain definition -1/2 sum J_ij s_i s_j."""
+    n, batch = 130, 40
+    rng = np.random.default_rng(8)
+    inst = sk_instance(n, 5)
+    s = random_spins(batch, n, 6)
+    s[5, 7], s[20, 0], s[39, 129] = 0, 2, 0
+    E = to_np(fv.energy(fv.couplings(inst), torch.as_tensor(s, device="cuda"))).astype(np.float64)
+    x, J = s.astype(np.float64), inst.dense.astype(np.float32).astype(np.float64)
+    ref = -0.5 * ((x @ J) * x).sum(1)
+    assert np.max(np.abs(E - ref)) / n <= 1e-5
