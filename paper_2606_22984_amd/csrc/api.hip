@@ -338,7 +338,7 @@ int fvan_muon_step(fvan_model* m, const fvan_muon* opt, int64_t step, void* stre
   if (step < 1) return fail(FVAN_EINVAL, "step counts from 1");
   if (const char* why = check_muon(*opt)) return fail(FVAN_EINVAL, why);
   hipStream_t s = (hipStream_t)stream;
-  FVAN_HIP(launch_muon(m->cfg, m->params, m->grads, m->adam_m, m->adam_v, m->n_params, *opt, step, s));
+  FVAN_HIP(launch_muon(m->cfg, m->params, m->grads, m->adam_m, m->adam_v, m->n_params, *opt, step, m->fw.part, s));
   FVAN_HIP(launch_pack(m->cfg, m->params, m->wpack, s));
   return FVAN_OK;
 }

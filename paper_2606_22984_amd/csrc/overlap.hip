@@ -14,9 +14,8 @@
 // Overlaps concentrate on few bins, so the histogram is kept in up to 16 copies,
 // interleaved so that the lanes of a 16-lane row never meet on an address; one
 // copy per bin made the LDS atomics the bound.  With 64 x 64 blocks read straight
-// from L2 by every wave and one copy, 16384 samples of 1000 spins took 937 us; now
-// 249 us
-// (1.08e15 int8 operations/s); the atomics are about half of it.
+// from L2 by every wave and one copy, 16384 samples of 1000 spins took 936 us; now
+// 249 us (1.08e15 int8 operations/s), the atomics about half of it.
 #include <algorithm>
 #include <cmath>
 

@@ -164,3 +164,26 @@ def test_muon_rejects_bad_hyper_parameters():
         with pytest.raises(fv.FvanError):
             m.muon_step(1, **bad)
     assert np.array_equal(to_np(m.params), theta)
+
+
+@pytest.mark.parametrize("d,nh,steps", [(32, 2, 0), (32, 1, 1), (64, 4, 0), (64, 2, 1), (64, 4, 5), (128, 8, 0),
+                                        (128, 2, 1), (128, 8, 16)])
+def test_muon_step_every_width_and_step_count(d, nh, steps):
+    """One Muon step per model width (the single-workgroup kernels and the phase-per-launch ones), with no, one
+    and many Newton-Schulz iterations, against the oracle; tolerance as above."""
+    cfg = ModelConfig(11, d, 2, nh).with_mask(3, 2)
+    m, theta = make_model(cfg, 2, FP32, seed=4)
+    g = (np.random.default_rng(d + steps).standard_normal(theta.size) * 1e-2).astype(np.float32)
+    hyper = dict(lr=2e-2, momentum=0.9, weight_decay=0.05, rms_scale=0.2, ns_eps=1e-7, ns_steps=steps, adam_lr=1e-2)
+    m.grads.copy_(torch.as_tensor(g, device="cuda"))
+    say(f"muon d={d} steps={steps}")
+    m.muon_step(1, **hyper)
+    torch.cuda.synchronize()
+    z = np.zeros(theta.size)
+    ref, _, _ = muon.muon_update(theta.astype(np.float64), g.astype(np.float64), z, z, 1, cfg, **hyper)
+    mask = muon.muon_entries(cfg)
+    err = np.abs(to_np(m.params).astype(np.float64) - ref)
+    say(f"  max |dW| matrices {err[mask].max():.2e}")
+    assert err[mask].max() <= _tol_w(ref, hyper["lr"], 0.2 * math.sqrt(4 * d))
+    assert err[~mask].max() <= 1e-6
+    assert not torch.any(m.grads)
