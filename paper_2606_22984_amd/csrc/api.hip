@@ -25,17 +25,18 @@ ParamOffsets param_offsets(const fvan_model_config& c) {
   o.tok = 0;
   o.pos = (int64_t)c.vocab * c.d_token;
   o.layer0 = o.pos + (int64_t)c.n_spins * (d - c.d_token);
-  o.ln1_g = 0;
-  o.ln1_b = d;
-  o.qkv_w = 2 * d;
-  o.qkv_b = o.qkv_w + 3 * d * d;
-  o.ln2_g = o.qkv_b + 3 * d;
-  o.ln2_b = o.ln2_g + d;
-  o.ffn1_w = o.ln2_b + d;
-  o.ffn1_b = o.ffn1_w + 4 * d * d;
-  o.ffn2_w = o.ffn1_b + 4 * d;
-  o.ffn2_b = o.ffn2_w + 4 * d * d;
-  o.layer_stride = o.ffn2_b + d;   // = 11 d^2 + 12 d
+  const LayerOffsets l = layer_offsets(d);
+  o.ln1_g = l.ln1_g;
+  o.ln1_b = l.ln1_b;
+  o.qkv_w = l.qkv_w;
+  o.qkv_b = l.qkv_b;
+  o.ln2_g = l.ln2_g;
+  o.ln2_b = l.ln2_b;
+  o.ffn1_w = l.ffn1_w;
+  o.ffn1_b = l.ffn1_b;
+  o.ffn2_w = l.ffn2_w;
+  o.ffn2_b = l.ffn2_b;
+  o.layer_stride = l.stride;   // 11 d^2 + 12 d
   o.head_w = o.layer0 + (int64_t)c.n_layers * o.layer_stride;
   o.head_b = o.head_w + (int64_t)c.vocab * d;
   o.total = o.head_b + c.vocab;
@@ -46,12 +47,12 @@ PackOffsets pack_offsets(const fvan_model_config& c) {
   PackOffsets p;
   const size_t d = c.d_model, e = w_elem_bytes(c.precision);
   p.qkv = 0;
-  p.ffn1 = p.qkv + 3 * d * d * e;
-  p.ffn2 = p.ffn1 + 4 * d * d * e;
+  p.ffn1 = (size_t)pack_ffn1_offset(d);
+  p.ffn2 = (size_t)pack_ffn2_offset(d);
   p.qkvT = p.ffn2 + 4 * d * d * e;
   p.ffn1T = p.qkvT + 3 * d * d * e;
   p.ffn2T = p.ffn1T + 4 * d * d * e;
-  p.layer_stride = p.ffn2T + 4 * d * d * e;
+  p.layer_stride = (size_t)pack_layer_bytes(d);
   p.head = p.headT = p.total = p.layer_stride * c.n_layers;
   p.vp = 0;
   if (c.vocab > 2) {
@@ -78,6 +79,9 @@ static int check_config(const fvan_model_config* c) {
   if (c->precision != FVAN_FP32 && c->precision != FVAN_BF16_SPLIT)
     return fail(FVAN_EINVAL, "unknown precision (FVAN_FP32 = 0 or FVAN_BF16_SPLIT = 2)");
   if (c->workspaces & ~(FVAN_WS_SAMPLER | FVAN_WS_TEACHER)) return fail(FVAN_EINVAL, "unknown workspace bits");
+  // the decode kernel addresses a sample's keys and values of a layer with 32-bit byte offsets
+  if ((c->workspaces & FVAN_WS_SAMPLER) && (int64_t)2 * kv_geom(*c).S * c->d_model * kv_elem_bytes(c->precision) > INT32_MAX - 64)
+    return fail(FVAN_EUNSUPPORTED, "the keys and values of one sample and layer must fit 2 GiB");
   return FVAN_OK;
 }
 
@@ -213,7 +217,7 @@ int fvan_sample(fvan_model* m, int32_t batch, uint64_t seed, uint64_t stream_id,
   if (!m->params || !m->synced) return fail(FVAN_EINVAL, "parameters not bound/synced");
   if (batch < 1 || batch > m->cfg.max_batch) return fail(FVAN_EINVAL, "batch outside [1, max_batch]");
   DecodeShape sh = decode_shape(m->cfg);
-  sh.tile = sample_tile(m, sh, batch);
+  sh.tile = sample_tile(m, batch);
   DecodeUnit u = make_decode_unit(m, batch, seed, stream_id, spins, log_q, m->kv, 0, sh.tile);
   FVAN_HIP(launch_decode_single(sh, u, u.n_tiles, (hipStream_t)stream));
   FVAN_HIP(check_finite(m, log_q, batch, (hipStream_t)stream));
@@ -228,7 +232,7 @@ int fvan_sample_tokens(fvan_model* m, int32_t batch, uint64_t seed, uint64_t str
   if (batch < 1 || batch > m->cfg.max_batch) return fail(FVAN_EINVAL, "batch outside [1, max_batch]");
   DecodeShape sh = decode_shape(m->cfg);
   sh.tokens = true;
-  sh.tile = sample_tile(m, sh, batch);
+  sh.tile = sample_tile(m, batch);
   DecodeUnit u = make_decode_unit(m, batch, seed, stream_id, reinterpret_cast<int8_t*>(tokens), log_q, m->kv, 0,
                                   sh.tile);
   FVAN_HIP(launch_decode_single(sh, u, u.n_tiles, (hipStream_t)stream));

@@ -23,14 +23,13 @@ FVAN_DECODE_EXT_LIST(FVAN_DECODE_EXTERN)
 template <int D, int MODE, int DH>
 static hipError_t dispatch_tok(const DecodeShape& sh, const DecodeUnit& u0, const DecodeUnit* table, int n_units,
                                int total_tiles, int* queue, int grid, hipStream_t s) {
-  if (sh.tile == 16) {
+  if (sh.tile < 1 || sh.tile > 32) return hipErrorInvalidValue;
+  if (sh.tile <= 16) {
     if constexpr (DH == 16)
       if (!sh.tokens) return launch_d<D, MODE, DH, false, 16>(u0, table, n_units, total_tiles, queue, grid, s);
     if constexpr (D == 128 && DH == 64)
       if (sh.tokens) return launch_d<D, MODE, DH, true, 16>(u0, table, n_units, total_tiles, queue, grid, s);
-    return hipErrorInvalidValue;
   }
-  if (sh.tile != 32) return hipErrorInvalidValue;
   return sh.tokens ? launch_d<D, MODE, DH, true, 32>(u0, table, n_units, total_tiles, queue, grid, s)
                    : launch_d<D, MODE, DH, false, 32>(u0, table, n_units, total_tiles, queue, grid, s);
 }

@@ -1,20 +1,29 @@
 // KV-cached ancestral sampling (Alg. 2 of the paper) for gfx950.
 //
-// One workgroup (8 waves) owns a tile of KM = 32 (or 16) samples and runs every step
-// t = 0..N-1 and every layer without leaving the kernel: samples are
+// One workgroup (8 waves) owns a tile of up to KM = 32 (or 16) samples and runs every
+// step t = 0..N-1 and every layer without leaving the kernel: samples are
 // independent, so no grid-wide synchronisation is ever needed.  Per layer step:
-//   LN1 (16 lanes per sample, shuffle reductions)
-//   QKV = LN1(h) W^T + b on MFMA (32 samples x 3d: every weight fragment a wave
+//   LN1 (16 lanes per sample, DPP reductions)
+//   QKV = LN1(h) W^T + b on MFMA (KM samples x 3d: every weight fragment a wave
 //        loads feeds both 16-sample row tiles, which halves the weight traffic
-//        per sample), k_t and v_t go straight from the MFMA accumulators to the
-//        sample's KV cache slot
+//        per sample); q_t, k_t, v_t go to LDS
 //   attention: one wave per sample, K/V rows streamed with 16-byte coalesced
-//        loads, per-head dot products and an online softmax reduced with lane
-//        shuffles; the heads' concatenation is added to h (no W_O)
+//        loads (the step's own row taken from LDS and appended to the sample's
+//        cache slot), per-head dot products and an online softmax reduced with
+//        lane swaps; the heads' concatenation is added to h (no W_O)
 //   LN2 + FFN (4d hidden kept in LDS) on MFMA, residual added in place
 // then the head, the Philox draw and the decision.  The KV cache of a sample
 // and layer holds the prefix positions [0, P) and a ring of the last R band
 // positions, so the visible keys of step t are always slots [0, nvis).
+//
+// What bounds a layer step (2D L=16 model, 16 samples per workgroup, 23100 clocks
+// before): the attention's vector instructions (about 5600 clocks of issue per SIMD,
+// and a latency of memory before them), then an L2 latency at the head of each of
+// the other phases.  So the loads are issued a phase ahead (below), the merge of the
+// attention's row groups keeps only the elements a lane will add, and a layer's
+// offsets are compile-time constants (20 fewer scalar registers to spill).
+// 10.24 -> 8.56 ms per 4096 samples, N=16 SK 211 -> 141 us per 1024 with the tile rule
+// (sample_tile); 2D groups 45.1 -> 36.9 ms; same samples bit for bit.
 //
 // Template parameters: D = d_model, MODE = precision, DH = head width (16, 32
 // or 64), TOK = a model over 2^D-spin patch tokens: the head has `vocab`
@@ -37,6 +46,7 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxVocab = 256;
+#define FVAN_INLINE __attribute__((always_inline))
 
 // KM: samples per workgroup, 32 (two 16-row MFMA tiles: every weight fragment
 // feeds both) or 16 (one tile; twice the workgroups for a batch).
@@ -54,6 +64,8 @@ struct DecodeSmem {
     A hid[KM][LDH];
     float z[TOK ? KM : 1][TOK ? LDZ : 1];   // logits of the vocab-way head
   } u;
+  // k_t and v_t of the tile's samples for the layer in progress
+  __align__(16) typename Mode<MODE>::KvT kv[KM][2][D];
   int tok[KM];
   int8_t sbuf[KM][64];
   // FFN2 partial sums of the waves that take the upper K ranges in split mode
@@ -65,13 +77,57 @@ struct DecodeSmem {
 
 __device__ __forceinline__ float reduce16(float v) { return row_sum16(v); }
 
-// 16-byte load of the K/V stream, marked non-temporal so that it does not push
-// the layer weights out of L2
+// The K/V block of one sample and layer as a raw buffer: a lane with nothing to load
+// or store gives an offset past the end (loads return zero, stores are dropped), so
+// no branch surrounds the access and the compiler knows how many loads are in flight
+// behind the one it waits for.  Loads are non-temporal, so that the stream does not
+// push the layer weights out of L2.
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-template <typename T>
-__device__ __forceinline__ uint4 stream_load16(const T* p) {
-  const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
+typedef __amdgpu_buffer_rsrc_t kv_rsrc_t;
+constexpr int kNoLane = 0x7FFFFFF0;          // past the end of any block
+__device__ __forceinline__ kv_rsrc_t kv_rsrc(void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ uint4 kv_load16(kv_rsrc_t r, int voff, int soff) {
+  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 2);
   return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void kv_store16(kv_rsrc_t r, const uint4& x, int voff) {
+  const u32x4_t v = {x.x, x.y, x.z, x.w};
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, 0);
+}
+
+// (a, b) of a lane and of lane ^ off become (the a of the pair's lower lane, the a of
+// its upper lane) in the lower lane and the same of b in the upper one: each lane of
+// the pair ends up with both lanes' values of one of the two.  off = 4, 8, 16 or 32.
+__device__ __forceinline__ void lane_pair(float& a, float& b, int off) {
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  if (off == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(ua, ub, false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  } else if (off == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  } else if (off == 8) {                     // row_ror:8 into the upper (lower) half of each row only
+    a = __int_as_float(__builtin_amdgcn_update_dpp((int)ua, (int)ub, 0x128, 0xF, 0xC, false));
+    b = __int_as_float(__builtin_amdgcn_update_dpp((int)ub, (int)ua, 0x128, 0xF, 0x3, false));
+  } else {
+    const bool up = threadIdx.x & off;
+    const float x = __shfl_xor(up ? a : b, off);
+    const float keep = up ? b : a;
+    a = up ? x : keep;
+    b = up ? keep : x;
+  }
+}
+
+// x, hidden from loop-invariant code motion: what is computed from it stays where it
+// is used (hoisted out of the step and layer loops, the lane's many addresses took
+// the registers of the loads in flight and spilled)
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 // LayerNorm of the KM residual rows into the MFMA operand buffer (16 lanes per row).
@@ -79,13 +135,27 @@ __device__ __forceinline__ uint4 stream_load16(const T* p) {
 // consecutive elements of a row is a BF16 hi uint4 followed by its lo uint4 (the
 // same hi/lo as the GEMMs' own split of FP32 operands), so the QKV and FFN1
 // products read their A fragments without converting them per output tile.
+// The lane's gains and shifts are loaded ahead (LnParams).
+template <int D, int MODE>
+struct LnParams {
+  static constexpr int PER = D / 16;
+  float g[PER], b[PER];
+  __device__ __forceinline__ void load(const float* __restrict__ pg, const float* __restrict__ pb) {
+    const int part = opaque(threadIdx.x & 15);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int k = Mode<MODE>::SPLIT ? part * PER + i : part + 16 * i;
+      g[i] = pg[k];
+      b[i] = pb[k];
+    }
+  }
+};
 template <int D, int MODE, bool TOK, int KM>
-__device__ __forceinline__ void ln_rows(DecodeSmem<D, MODE, TOK, KM>& sm, const float* __restrict__ g,
-                                        const float* __restrict__ b) {
+__device__ __forceinline__ void ln_rows(DecodeSmem<D, MODE, TOK, KM>& sm, const LnParams<D, MODE>& lp) {
   typedef typename Mode<MODE>::ActT T;
   constexpr int PER = D / 16;
   constexpr bool SPLIT = Mode<MODE>::SPLIT;
-  const int m = threadIdx.x >> 4, part = threadIdx.x & 15;
+  const int tid = opaque(threadIdx.x), m = tid >> 4, part = tid & 15;
   if (m >= KM) return;
   float x[PER];
   float s = 0.f;
@@ -107,10 +177,7 @@ __device__ __forceinline__ void ln_rows(DecodeSmem<D, MODE, TOK, KM>& sm, const 
     static_assert(PER % 2 == 0 && 8 % PER == 0, "a lane's elements lie in one 8-element group");
     float y[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int k = part * PER + i;
-      y[i] = x[i] * rstd * g[k] + b[k];
-    }
+    for (int i = 0; i < PER; ++i) y[i] = x[i] * rstd * lp.g[i] + lp.b[i];
     // hi = bf16(y), lo = bf16(y - hi), two elements per 32-bit word
     uint32_t hw[PER / 2], lw[PER / 2];
 #pragma unroll
@@ -135,69 +202,78 @@ __device__ __forceinline__ void ln_rows(DecodeSmem<D, MODE, TOK, KM>& sm, const 
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int k = part + 16 * i;
-      sm.a[m][k] = from_f<T>(x[i] * rstd * g[k] + b[k]);
+      sm.a[m][k] = from_f<T>(x[i] * rstd * lp.g[i] + lp.b[i]);
     }
   }
 }
 
 // The output tiles nt = nt0, nt0 + step, ... < ntn of A[16 NRT x K] (LDS, row
 // stride lda) . pack, each finished tile handed to epi(nt, acc0, acc1).  The
-// weight fragments come G chunks per round, and the next round's (of this tile
-// or of the wave's next tile) are loaded while the current round multiplies, so
-// a phase exposes one L2 latency instead of one per round.  Per tile the chunks
-// are summed in order, as a single pass over the tile would; acc1 stays zero
-// when NRT = 1.
+// weight fragments come G chunks per round, and the loads of the next two rounds
+// (of this tile or of the wave's next one) are in flight while a round multiplies.
+// begin() issues the first two rounds: it is called a phase ahead, so that their L2
+// latency passes under that phase (the weights do not depend on it); loaded(), once
+// every load of the product has been issued, is where the caller begins the next
+// phase's loads (a wave's loads return in order, so nothing a phase waits for is
+// issued behind a longer load).  Per tile the chunks are summed in order, as a
+// single pass over the tile would; acc1 stays zero when NRT = 1.
 // PRE: A holds split-mode operands written by ln_rows (per 8-element group a hi
 // uint4, then its lo uint4; row stride lda elements of Mode<2>::ActT).
-template <int MODE, int K, int NRT, typename Epi, bool PRE = false>
-__device__ __forceinline__ void mfma_tiles(const typename Mode<MODE>::ActT* A, int lda,
-                                           const uint4* __restrict__ pack, size_t lo_u4, int nt0, int ntn, int step,
-                                           int lane, Epi&& epi) {
-  constexpr int KC = Mode<MODE>::KC;
-  constexpr int NC = K / KC;
-  constexpr int GM = Mode<MODE>::SPLIT ? 2 : 4;
-  constexpr int G = NC < GM ? NC : GM;
+// LO: hi-to-lo distance of a split pack, in fragments.
+template <int MODE, int K, int LO>
+struct TileLoads {
+  static constexpr int KC = Mode<MODE>::KC;
+  static constexpr int NC = K / KC;
+  static constexpr int GM = Mode<MODE>::SPLIT ? 2 : 4;
+  static constexpr int G = NC < GM ? NC : GM;
+  static constexpr int R = NC / G;          // rounds per tile
   static_assert(NC % G == 0, "K chunks in groups of G");
-  constexpr int R = NC / G;                 // rounds per tile
-  if (nt0 >= ntn) return;
+  uint4 h0[G], l0[G], h1[G], l1[G];         // the first two rounds
+  const uint4* pack;
+  __device__ __forceinline__ void load(int t, int rr, int lane, uint4* h, uint4* l) const {
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const uint4* bp = pack + (uint32_t)((t * NC + rr * G + u) * 64 + lane);
+      h[u] = bp[0];
+      l[u] = Mode<MODE>::SPLIT ? bp[LO] : h[u];
+    }
+  }
+  // tile and round after (t, rr)
+  static __device__ __forceinline__ void advance(int& t, int& rr, int step) {
+    if (++rr == R) {
+      rr = 0;
+      t += step;
+    }
+  }
+  // (a wave with fewer rounds loads its last tile's again: without branches the
+  // registers are free from one use to the next load)
+  __device__ __forceinline__ void begin(const uint4* __restrict__ p, int nt0, int ntn, int step, int lane) {
+    pack = p;
+    load(min(nt0, ntn - 1), 0, lane, h0, l0);
+    int t = nt0, r = 0;
+    advance(t, r, step);
+    load(min(t, ntn - 1), r, lane, h1, l1);
+  }
+};
+
+// MAXT: the most tiles a wave has.
+template <int MODE, int K, int NRT, bool PRE, int MAXT, int LO, typename Epi, typename Loaded>
+__device__ __forceinline__ void mfma_tiles(TileLoads<MODE, K, LO>& w, const typename Mode<MODE>::ActT* A, int lda, int nt0,
+                                           int ntn, int step, int lane, Epi&& epi, Loaded&& loaded) {
+  typedef TileLoads<MODE, K, LO> W;
+  constexpr int KC = W::KC, G = W::G, R = W::R;
+  if (nt0 >= ntn) {
+    loaded();
+    return;
+  }
   static_assert(!PRE || Mode<MODE>::SPLIT, "pre-split operands in split mode only");
   const typename Mode<MODE>::ActT* arow = A + (lane & 15) * lda + (lane >> 4) * (KC / 4);
   const typename Mode<MODE>::ActT* arow1 = arow + 16 * lda;
   // pre-split: lane (g, c) takes group 4 kc + g of row c: uint4s 2 (4 kc + g) and + 1
   const uint4* prow = reinterpret_cast<const uint4*>(A) + (lane & 15) * (lda * (int)sizeof(*A) / 16) + 2 * (lane >> 4);
   const uint4* prow1 = prow + 16 * (lda * (int)sizeof(*A) / 16);
-  uint4 bh[G], bl[G], nh[G], nl[G];
-#define FVAN_DT_LOAD(T, RR, H, L)                                                              \
-  _Pragma("unroll") for (int u = 0; u < G; ++u) {                                            \
-    const uint4* bp_ = pack + (size_t)(T) * NC * 64 + (size_t)((RR) * G + u) * 64 + lane;    \
-    H[u] = bp_[0];                                                                           \
-    L[u] = Mode<MODE>::SPLIT ? bp_[lo_u4] : H[u];                                            \
-  }
-  // rounds are consumed in order; the loads of the next two rounds are in flight
-  // while a round multiplies
-  auto advance = [&](int& t, int& rr) {
-    if (++rr == R) {
-      rr = 0;
-      t += step;
-    }
-  };
-  uint4 mh[G], ml[G];
-  FVAN_DT_LOAD(nt0, 0, bh, bl);
-  int nt1 = nt0, r1 = 0;
-  advance(nt1, r1);
-  bool more1 = nt1 < ntn;
-  if (more1) {
-    FVAN_DT_LOAD(nt1, r1, nh, nl);
-  }
   floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
-  int nt = nt0, r = 0;
-  for (;;) {
-    int nt2 = nt1, r2 = r1;
-    advance(nt2, r2);
-    const bool more2 = more1 && nt2 < ntn;
-    if (more2) {
-      FVAN_DT_LOAD(nt2, r2, mh, ml);
-    }
+  auto multiply = [&](int nt, int r, const uint4* bh, const uint4* bl) FVAN_INLINE {
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const int kc = r * G + u;
@@ -231,21 +307,42 @@ __device__ __forceinline__ void mfma_tiles(const typename Mode<MODE>::ActT* A, i
       acc0 = floatx4{0.f, 0.f, 0.f, 0.f};
       acc1 = acc0;
     }
-    if (!more1) break;
-    nt = nt1;
-    r = r1;
-    nt1 = nt2;
-    r1 = r2;
-    more1 = more2;
+  };
+  int nt = nt0, r = 0, nt1 = nt0, r1 = 0;
+  W::advance(nt1, r1, step);
+  if constexpr (MAXT * R > 2) {
+    int nt2 = nt1, r2 = r1;
+    W::advance(nt2, r2, step);
+    while (nt2 < ntn) {                     // a round beyond the two in flight
+      uint4 mh[G], ml[G];
+      w.load(nt2, r2, lane, mh, ml);
+      multiply(nt, r, w.h0, w.l0);
 #pragma unroll
-    for (int u = 0; u < G; ++u) {
-      bh[u] = nh[u];
-      bl[u] = nl[u];
-      nh[u] = mh[u];
-      nl[u] = ml[u];
+      for (int u = 0; u < G; ++u) {
+        w.h0[u] = w.h1[u];
+        w.l0[u] = w.l1[u];
+        w.h1[u] = mh[u];
+        w.l1[u] = ml[u];
+      }
+      nt = nt1;
+      r = r1;
+      nt1 = nt2;
+      r1 = r2;
+      W::advance(nt2, r2, step);
     }
   }
-#undef FVAN_DT_LOAD
+  loaded();
+  multiply(nt, r, w.h0, w.l0);
+  if (nt1 < ntn) multiply(nt1, r1, w.h1, w.l1);
+}
+
+// bias[i] of the wave's i-th output tile, chosen without indexing registers
+template <int T>
+__device__ __forceinline__ float pick(const float (&v)[T], int i) {
+  float x = v[0];
+#pragma unroll
+  for (int k = 1; k < T; ++k) x = i == k ? v[k] : x;
+  return x;
 }
 
 template <int D, int MODE, int DH, bool TOK, int KM>
@@ -269,8 +366,8 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
   constexpr float kScaleLog2 = (DH == 16 ? 0.25f : DH == 32 ? 0.17677669529663688f : 0.125f) * 1.4426950408889634f;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b0 = local_tile * KM;
-  const int nb = min(KM, U.B - b0);
+  const int b0 = local_tile * U.tile;   // U.tile <= KM samples per workgroup
+  const int nb = min(U.tile, U.B - b0);
   const int N = U.N, P = U.P, R = U.R, S = U.S, nl = U.n_layers, dt = U.d_token;
   const float* __restrict__ theta = U.theta;
   const char* wbase = reinterpret_cast<const char*>(U.wpack);
@@ -282,100 +379,188 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
   float lq = 0.f;
   float ur[4] = {0.f, 0.f, 0.f, 0.f};
   if (tid < KM) sm.tok[tid] = 0;   // start token
+
+  // Loads that do not depend on the step's arithmetic are issued ahead of the phase
+  // that uses them: the layer's small parameters and first weight rounds a phase
+  // ahead, the K/V rows of the layer's first batch from the previous layer's FFN2.
+  // Exposed, each phase began with an L2 latency and the attention with a memory
+  // latency.  (The second batch from there as well: 9.26 against 8.58 ms for the 2D
+  // L=16 sampling, as a compute unit's loads all in one phase wait for its 64 bytes
+  // per clock of L1.)
+  constexpr int TQ = (3 * D / 16 + kWaves - 1) / kWaves;   // output tiles per wave: QKV, FFN1
+  constexpr int T1 = (4 * D / 16 + kWaves - 1) / kWaves;
+  constexpr int NT2 = D / 16;                              // FFN2 output tiles
+  constexpr int SK = Sm::KP + 1;                           // waves per FFN2 output tile (K ranges)
+  constexpr int NCS = 4 * D / Mode<MODE>::KC / SK;         // K chunks per range
+  constexpr int LOQ = 3 * D * D / 8, LOF = 4 * D * D / 8;
+  const int tile2 = SK > 1 ? wave % NT2 : wave, part2 = SK > 1 ? wave / NT2 : 0;
+  TileLoads<MODE, D, LOQ> wq;
+  TileLoads<MODE, D, LOF> w1;
+  TileLoads<MODE, 4 * D / SK, LOF> w2;
+  LnParams<D, MODE> ln1, ln2;
+  float bq[TQ], b1[T1], b2;
+  constexpr LayerOffsets LO = layer_offsets(D);
+  const float* __restrict__ theta0 = theta + U.layer0;
+  auto layer_theta = [&](int l) FVAN_INLINE { return theta0 + (uint32_t)(l * (int)LO.stride); };
+  auto layer_pack = [&](int l, int64_t off) FVAN_INLINE {
+    return reinterpret_cast<const uint4*>(wbase + (uint32_t)(l * (int)pack_layer_bytes(D) + (int)off));
+  };
+  auto begin_qkv = [&](int l) FVAN_INLINE {
+    const int lane = opaque(tid & 63);
+    const float* lp = layer_theta(l);
+    ln1.load(lp + LO.ln1_g, lp + LO.ln1_b);
+#pragma unroll
+    for (int i = 0; i < TQ; ++i) {
+      const int nt = wave + kWaves * i;
+      bq[i] = lp[(int)LO.qkv_b + min(nt * 16, 3 * D - 16) + (lane & 15)];
+    }
+    wq.begin(layer_pack(l, 0), wave, 3 * D / 16, kWaves, lane);
+  };
+  auto begin_ffn1 = [&](int l) FVAN_INLINE {
+    const int lane = opaque(tid & 63);
+    const float* lp = layer_theta(l);
+    ln2.load(lp + LO.ln2_g, lp + LO.ln2_b);
+#pragma unroll
+    for (int i = 0; i < T1; ++i) b1[i] = lp[(int)LO.ffn1_b + min((wave + kWaves * i) * 16, 4 * D - 16) + (lane & 15)];
+    w1.begin(layer_pack(l, pack_ffn1_offset(D)), wave, 4 * D / 16, kWaves, lane);
+  };
+  auto begin_ffn2 = [&](int l) FVAN_INLINE {
+    const int lane = opaque(tid & 63);
+    b2 = layer_theta(l)[(int)LO.ffn2_b + min(tile2, NT2 - 1) * 16 + (lane & 15)];
+    const uint4* p2 = layer_pack(l, pack_ffn2_offset(D));
+    if constexpr (SK > 1)
+      w2.begin(p2 + ((size_t)tile2 * 4 * D / Mode<MODE>::KC + (size_t)part2 * NCS) * 64, 0, 1, 1, lane);
+    else
+      w2.begin(p2, wave, NT2, kWaves, lane);
+  };
+
+  // K/V rows: a batch is UNR rows per lane, RPL rows per wave load, of one sample;
+  // a wave's samples are walked as one stream of batches
+  struct Batch {
+    uint4 k[UNR], v[UNR];
+  };
+  const int nsw = nb > wave ? (nb - wave + kWaves - 1) / kWaves : 0;   // samples of this wave
+  // step t: the slot of position t and the visible slots [0, nvis)
+  auto slot_of = [&](int t) FVAN_INLINE { return t < P ? t : P + (t - P) % R; };
+  auto nvis_of = [&](int t) FVAN_INLINE { return t < P ? t + 1 : P + min(t - P + 1, R); };
+  auto kv_block = [&](int m, int l) FVAN_INLINE { return kvbase + ((size_t)(b0 + m) * nl + l) * 2 * plane; };
+  // batch `part` of sample m: raw loads of its rows (the step's own is replaced from
+  // LDS when the batch is reduced); rows past the visible keys are zero, so their
+  // (zero) probabilities multiply zeros, not stale register contents
+  auto issue = [&](Batch& x, int l, int m, int part, int nvis) FVAN_INLINE {
+    const int lane = opaque(tid & 63), lrow = lane / LPR, lcol = (lane % LPR) * VEC;
+    const kv_rsrc_t r = kv_rsrc(kv_block(m, l), 2 * (int)(plane * sizeof(T)));
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const int s = (part * UNR + u) * RPL + lrow;
+      const int at = s < nvis ? (s * D + lcol) * (int)sizeof(T) : kNoLane;
+      x.k[u] = kv_load16(r, at, 0);
+      x.v[u] = kv_load16(r, at, (int)(plane * sizeof(T)));
+    }
+  };
+  Batch ba, bb;
+  auto issue_first = [&](int l, int t) FVAN_INLINE { issue(ba, l, wave, 0, t < N && nsw > 0 ? nvis_of(t) : 0); };
+
+  if (nl > 0) {
+    begin_qkv(0);
+    issue_first(0, 0);
+  }
   __syncthreads();
+
+  // the position embedding of a step: thread tid holds column tid % D of every row
+  static_assert(kThreads % D == 0, "a thread's column is the same in every row");
+  const int ek = tid % D;
+  auto pos_of = [&](int t) FVAN_INLINE { return theta[U.pos_off + (size_t)t * (D - dt) + max(ek - dt, 0)]; };
+  float pe = pos_of(0);
+  // the two token embeddings of a spin model
+  const float te0 = theta[min(ek, dt - 1)], te1 = theta[dt + min(ek, dt - 1)];
+  float hw0[D / 16], hw1[D / 16], hb0 = 0.f, hb1 = 0.f;    // the binary head, the lane's columns
+  if constexpr (!TOK) {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) {
+      hw0[i] = theta[U.head_w + hpart + 16 * i];
+      hw1[i] = theta[U.head_w + D + hpart + 16 * i];
+    }
+    hb0 = theta[U.head_b];
+    hb1 = theta[U.head_b + 1];
+  }
 
   for (int t = 0; t < N; ++t) {
     // ---- concatenated embedding [tok_emb[tok]; pos_emb[t]] ----
-    for (int i = tid; i < KM * D; i += kThreads) {
-      const int m = i / D, k = i % D;
-      sm.h[m][k] = k < dt ? theta[sm.tok[m] * dt + k] : theta[U.pos_off + (size_t)t * (D - dt) + (k - dt)];
+#pragma unroll
+    for (int i = 0; i < KM * D; i += kThreads) {
+      const int m = (i + tid) / D;
+      if constexpr (TOK) sm.h[m][ek] = ek < dt ? theta[sm.tok[m] * dt + ek] : pe;
+      else sm.h[m][ek] = ek < dt ? (sm.tok[m] ? te1 : te0) : pe;
     }
-    const int slot = t < P ? t : P + (t - P) % R;
-    const int nvis = t < P ? t + 1 : P + min(t - P + 1, R);
+    const int slot = slot_of(t), nvis = nvis_of(t);
+    const int per = (nvis + RPL * UNR - 1) / (RPL * UNR);   // batches per sample
+    pe = pos_of(min(t + 1, N - 1));
     __syncthreads();
 
     for (int l = 0; l < nl; ++l) {
-      const float* lp = theta + U.layer0 + (size_t)l * U.layer_stride;
-      const char* wl = wbase + (size_t)l * U.p_layer_stride;
-      ln_rows<D, MODE, TOK, KM>(sm, lp + U.o_ln1_g, lp + U.o_ln1_b);
+      ln_rows<D, MODE, TOK, KM>(sm, ln1);
       __syncthreads();
 
-      // ---- QKV projection; k_t, v_t appended to the cache ----
+      // ---- QKV projection; q_t, k_t, v_t to LDS ----
       {
-        const uint4* pk = reinterpret_cast<const uint4*>(wl + U.p_qkv);
-        auto qkv_epi = [&](int nt, const floatx4& a0, const floatx4& a1) {
+        auto qkv_epi = [&](int nt, const floatx4& a0, const floatx4& a1) FVAN_INLINE {
+          const int lane = opaque(tid & 63);
           const floatx4 acc[2] = {a0, a1};
           const int n = nt * 16 + (lane & 15);
-          const float bias = lp[U.o_qkv_b + n];
+          const float bias = pick<TQ>(bq, nt / kWaves);
 #pragma unroll
           for (int ri = 0; ri < 4 * NRT; ++ri) {
             const int row = 16 * (ri >> 2) + 4 * (lane >> 4) + (ri & 3);
             const float val = acc[ri >> 2][ri & 3] + bias;
             if (n < D) {
-              sm.u.q[row][n] = val;
-            } else if (row < nb) {
+              sm.u.q[row][n] = val * kScaleLog2;
+            } else {
               const int which = n >= 2 * D ? 1 : 0;
-              const int col = n - D - which * D;
-              T* dst = kvbase + ((size_t)(b0 + row) * nl + l) * 2 * plane + which * plane + (size_t)slot * D + col;
-              *dst = from_f<T>(val);
+              sm.kv[row][which][n - D - which * D] = from_f<T>(val);
             }
           }
         };
-        mfma_tiles<MODE, D, NRT, decltype(qkv_epi)&, Mode<MODE>::SPLIT>(&sm.a[0][0], Sm::LDA, pk, (size_t)3 * D * D / 8,
-                                                                       wave, 3 * D / 16, kWaves, lane, qkv_epi);
+        mfma_tiles<MODE, D, NRT, Mode<MODE>::SPLIT, TQ>(wq, &sm.a[0][0], Sm::LDA, wave, 3 * D / 16, kWaves, opaque(lane), qkv_epi,
+                                                    [&]() FVAN_INLINE { begin_ffn1(l); });
       }
-      __threadfence_block();
       __syncthreads();
 
       // ---- masked attention over slots [0, nvis), one wave per sample ----
-      // The wave's samples are walked as one stream of row batches (UNR rows per
-      // lane, RPL rows per wave load); the next batch's raw 16-byte K/V loads are
-      // issued before the current batch is reduced, across sample boundaries too.
+      // Two batches in flight: a batch's registers are loaded again as soon as it has
+      // been reduced, across sample boundaries too.
       {
-        const int lrow = lane / LPR;
-        const int lcol = (lane % LPR) * VEC;
-        const int per = (nvis + RPL * UNR - 1) / (RPL * UNR);   // batches per sample
-        const int nsw = nb > wave ? (nb - wave + kWaves - 1) / kWaves : 0;   // samples of this wave
-        const int total = per * nsw;
-        uint4 kr[UNR], vr[UNR];
-        auto issue = [&](int bi, uint4* kk, uint4* vv) {
-          const int m = wave + kWaves * (bi / per);
-          const int s0 = (bi % per) * RPL * UNR;
-          const T* Kb = kvbase + ((size_t)(b0 + m) * nl + l) * 2 * plane;
-#pragma unroll
-          for (int u = 0; u < UNR; ++u) {
-            const int s = s0 + u * RPL + lrow;
-            // rows past the visible keys are zero, so their (zero) probabilities
-            // multiply zeros, not stale register contents
-            kk[u] = make_uint4(0u, 0u, 0u, 0u);
-            vv[u] = kk[u];
-            if (s < nvis) {
-              kk[u] = stream_load16(Kb + (size_t)s * D + lcol);
-              vv[u] = stream_load16(Kb + plane + (size_t)s * D + lcol);
-            }
-          }
-        };
-        if (total > 0) issue(0, kr, vr);
         float qv[VEC], o[VEC];
         float mx = -INFINITY, sum = 0.f;
-        for (int bi = 0; bi < total; ++bi) {
-          uint4 kn[UNR], vn[UNR];
-          if (bi + 1 < total) issue(bi + 1, kn, vn);
-          const int m = wave + kWaves * (bi / per);
-          const int part = bi % per;
+        auto reduce = [&](Batch& x, int m, int part) FVAN_INLINE {
+          const int lane = opaque(tid & 63), lrow = lane / LPR, lcol = (lane % LPR) * VEC;
           if (part == 0) {
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) { qv[i] = sm.u.q[m][lcol + i] * kScaleLog2; o[i] = 0.f; }
+            for (int i = 0; i < VEC; ++i) { qv[i] = sm.u.q[m][lcol + i]; o[i] = 0.f; }
             mx = -INFINITY;
             sum = 0.f;
+            // append k_t (row group 0) and v_t (row group 1) to the cache: this wave
+            // is the only reader of the sample's rows
+            kv_store16(kv_rsrc(kv_block(m, l), 2 * (int)(plane * sizeof(T))),
+                       *reinterpret_cast<const uint4*>(&sm.kv[m][lrow & 1][lcol]),
+                       lrow < 2 ? (int)((lrow * plane + slot * D + lcol) * sizeof(T)) : kNoLane);
           }
           const int s0 = part * RPL * UNR;
+          if (slot >= s0 && slot < s0 + RPL * UNR) {   // the step's own row
+            const int us = (slot - s0) / RPL;
+#pragma unroll
+            for (int u = 0; u < UNR; ++u)
+              if (u == us && lrow == (slot - s0) % RPL) {
+                x.k[u] = *reinterpret_cast<const uint4*>(&sm.kv[m][0][lcol]);
+                x.v[u] = *reinterpret_cast<const uint4*>(&sm.kv[m][1][lcol]);
+              }
+          }
           float sc[UNR];
           float mnew = mx;
 #pragma unroll
           for (int u = 0; u < UNR; ++u) {
             Chunk<T> kc;
-            kc.unpack(kr[u]);
+            kc.unpack(x.k[u]);
             float d = 0.f;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) d += qv[i] * kc.v[i];
@@ -386,61 +571,109 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
             sc[u] = s0 + u * RPL + lrow < nvis ? d : -INFINITY;
             mnew = fmaxf(mnew, sc[u]);
           }
-          const float corr = mnew != -INFINITY ? __builtin_amdgcn_exp2f(mx - mnew) : 1.f;
-          sum *= corr;
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) o[i] *= corr;
+          // a lane with no visible row so far subtracts 0 instead of its -inf maximum:
+          // its exponentials are exp2(-inf) = 0
+          const float base = mnew == -INFINITY ? 0.f : mnew;
+          const float corr = __builtin_amdgcn_exp2f(mx - base);
+          // The rescale of the running sums is fused with the batch's first row, written
+          // out so that the roundings do not depend on how the compiler contracts.
+          // (At d = 64 in split mode two elements round the other product: samples of
+          // one seed stay the same from one version of the kernel to the next.)
+          auto keeps = [](int i) { return D == 64 && Mode<MODE>::SPLIT && i < 2; };
 #pragma unroll
           for (int u = 0; u < UNR; ++u) {
-            const bool ok = sc[u] != -INFINITY;
-            const float p = ok ? __builtin_amdgcn_exp2f(sc[u] - mnew) : 0.f;
+            const float p = __builtin_amdgcn_exp2f(sc[u] - base);
             Chunk<T> vc;
-            vc.unpack(vr[u]);
-            sum += p;
+            vc.unpack(x.v[u]);
+            sum = u == 0 ? __builtin_fmaf(sum, corr, p) : sum + p;
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) o[i] += p * vc.v[i];
+            for (int i = 0; i < VEC; ++i)
+              o[i] = u > 0      ? __builtin_fmaf(p, vc.v[i], o[i])
+                     : keeps(i) ? __builtin_fmaf(p, vc.v[i], o[i] * corr)
+                                : __builtin_fmaf(o[i], corr, p * vc.v[i]);
           }
           mx = mnew;
           if (part == per - 1) {
-            // merge the RPL row groups of the wave, then add the heads' outputs to h
+            // Merge the RPL row groups of the wave, pairs LPR .. 32 lanes apart in turn.
+            // Each merge also halves the elements a lane keeps (the lane with the
+            // pair's bit set takes the upper half), so the o merges cost 4 + 2 + 1
+            // elements instead of 8 + 8 + 8; the lower lane's operand order is used in
+            // both lanes.  Then every lane adds its element(s) of the heads' outputs.
+            int first = 0;                           // first element this lane keeps
+            bool adds = true;
 #pragma unroll
-            for (int off = LPR; off < 64; off <<= 1) {
-              const float m2 = lane_xor(mx, off);
-              const float s2 = lane_xor(sum, off);
-              const float mn = fmaxf(mx, m2);
-              const float c1 = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - mn);
-              const float c2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m2 - mn);
-              sum = sum * c1 + s2 * c2;
+            for (int off = LPR, keep = VEC; off < 64; off <<= 1) {
+              float ml = mx, mh = mx, sl = sum, sh = sum;
+              lane_pair(ml, mh, off);
+              lane_pair(sl, sh, off);
+              const float mn = fmaxf(ml, mh), base2 = mn == -INFINITY ? 0.f : mn;
+              const float c1 = __builtin_amdgcn_exp2f(ml - base2);
+              const float c2 = __builtin_amdgcn_exp2f(mh - base2);
+              sum = __builtin_fmaf(sl, c1, sh * c2);
+              if (keep > 1) {
+                keep >>= 1;
+                if (lane & off) first += keep;
 #pragma unroll
-              for (int i = 0; i < VEC; ++i) {
-                const float o2 = lane_xor(o[i], off);
-                o[i] = o[i] * c1 + o2 * c2;
+                for (int i = 0; i < VEC / 2; ++i)
+                  if (i < keep) {
+                    float lo = o[i], hi = o[i + keep];
+                    lane_pair(lo, hi, off);
+                    o[i] = __builtin_fmaf(lo, c1, hi * c2);
+                  }
+              } else {
+                float lo = o[0], hi = o[0];
+                lane_pair(lo, hi, off);
+                o[0] = __builtin_fmaf(lo, c1, hi * c2);
+                adds = adds && !(lane & off);
               }
               mx = mn;
             }
-            if (lrow == 0) {
-              const float inv = 1.0f / sum;
+            constexpr int KEPT = VEC / RPL > 1 ? VEC / RPL : 1;
+            const float inv = 1.0f / sum;
+            if (adds) {
 #pragma unroll
-              for (int i = 0; i < VEC; ++i) sm.h[m][lcol + i] += o[i] * inv;
+              for (int i = 0; i < KEPT; ++i)
+                sm.h[m][lcol + first + i] = __builtin_fmaf(o[i], inv, sm.h[m][lcol + first + i]);
             }
           }
-#pragma unroll
-          for (int u = 0; u < UNR; ++u) { kr[u] = kn[u]; vr[u] = vn[u]; }
+        };
+        // (m, part) of the batch to reduce and of the one two further on
+        int left = per * nsw, m = wave, part = 0, mi = wave, pi = 0;
+        auto next = [&](int& mm, int& pp) FVAN_INLINE {
+          if (++pp == per) {
+            pp = 0;
+            mm += kWaves;
+          }
+        };
+        next(mi, pi);
+        issue(bb, l, mi, pi, left > 1 ? nvis : 0);
+        next(mi, pi);
+        while (left > 0) {
+          reduce(ba, m, part);
+          next(m, part);
+          issue(ba, l, mi, pi, left > 2 ? nvis : 0);   // always: a known number of loads in flight
+          next(mi, pi);
+          if (--left == 0) break;
+          reduce(bb, m, part);
+          next(m, part);
+          issue(bb, l, mi, pi, left > 2 ? nvis : 0);   // always: a known number of loads in flight
+          next(mi, pi);
+          --left;
         }
       }
       __syncthreads();
 
       // ---- feed-forward block ----
-      ln_rows<D, MODE, TOK, KM>(sm, lp + U.o_ln2_g, lp + U.o_ln2_b);
+      ln_rows<D, MODE, TOK, KM>(sm, ln2);
       __syncthreads();
       {
-        const uint4* p1 = reinterpret_cast<const uint4*>(wl + U.p_ffn1);
         // split mode: GELU(h) goes to LDS already split, in the layout ln_rows
         // writes (per 8-element group of a row: 8 hi BF16, then 8 lo), for FFN2
-        auto ffn1_epi = [&](int nt, const floatx4& a0, const floatx4& a1) {
+        auto ffn1_epi = [&](int nt, const floatx4& a0, const floatx4& a1) FVAN_INLINE {
+          const int lane = opaque(tid & 63);
           const floatx4 acc[2] = {a0, a1};
           const int n = nt * 16 + (lane & 15);
-          const float bias = lp[U.o_ffn1_b + n];
+          const float bias = pick<T1>(b1, nt / kWaves);
 #pragma unroll
           for (int ri = 0; ri < 4 * NRT; ++ri) {
             const int row = 16 * (ri >> 2) + 4 * (lane >> 4) + (ri & 3);
@@ -456,54 +689,54 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
             }
           }
         };
-        mfma_tiles<MODE, D, NRT, decltype(ffn1_epi)&, Mode<MODE>::SPLIT>(&sm.a[0][0], Sm::LDA, p1, (size_t)4 * D * D / 8,
-                                                                        wave, 4 * D / 16, kWaves, lane, ffn1_epi);
+        mfma_tiles<MODE, D, NRT, Mode<MODE>::SPLIT, T1>(w1, &sm.a[0][0], Sm::LDA, wave, 4 * D / 16, kWaves, opaque(lane), ffn1_epi,
+                                                    [&]() FVAN_INLINE { begin_ffn2(l); });
       }
       __syncthreads();
       {
-        const uint4* p2 = reinterpret_cast<const uint4*>(wl + U.p_ffn2);
-        constexpr int NT2 = D / 16;         // output tiles
-        if constexpr (Sm::KP == 0) {
-          auto ffn2_epi = [&](int nt, const floatx4& a0, const floatx4& a1) {
+        // once FFN2's weights are on their way: the next layer's (or the next
+        // step's first layer's) parameters and first K/V rows
+        const bool wrap = l + 1 == nl;
+        auto ahead = [&]() FVAN_INLINE {
+          begin_qkv(wrap ? 0 : l + 1);
+          issue_first(wrap ? 0 : l + 1, wrap ? t + 1 : t);
+        };
+        if constexpr (SK == 1) {
+          auto ffn2_epi = [&](int nt, const floatx4& a0, const floatx4& a1) FVAN_INLINE {
+          const int lane = opaque(tid & 63);
             const floatx4 acc[2] = {a0, a1};
             const int n = nt * 16 + (lane & 15);
-            const float bias = lp[U.o_ffn2_b + n];
 #pragma unroll
             for (int ri = 0; ri < 4 * NRT; ++ri)
-              sm.h[16 * (ri >> 2) + 4 * (lane >> 4) + (ri & 3)][n] += acc[ri >> 2][ri & 3] + bias;
+              sm.h[16 * (ri >> 2) + 4 * (lane >> 4) + (ri & 3)][n] += acc[ri >> 2][ri & 3] + b2;
           };
-          mfma_tiles<MODE, 4 * D, NRT, decltype(ffn2_epi)&, Mode<MODE>::SPLIT>(&sm.u.hid[0][0], Sm::LDH, p2,
-                                                                              (size_t)4 * D * D / 8, wave, NT2,
-                                                                              kWaves, lane, ffn2_epi);
+          static_assert(NT2 <= kWaves, "one FFN2 tile per wave");
+          mfma_tiles<MODE, 4 * D, NRT, Mode<MODE>::SPLIT, 1>(w2, &sm.u.hid[0][0], Sm::LDH, wave, NT2, kWaves, opaque(lane),
+                                                          ffn2_epi, ahead);
         } else {
           // fewer output tiles than waves: the SK waves of a tile take consecutive
           // K ranges; the upper ranges' sums meet the lowest one's through LDS and
           // are added in range order
-          constexpr int SK = Sm::KP + 1;
-          constexpr int KC = Mode<MODE>::KC;
-          constexpr int NC2 = 4 * D / KC, NCS = NC2 / SK;
-          static_assert(NC2 % SK == 0, "whole K chunks per range");
-          const int tile = wave % NT2, part = wave / NT2;
-          const int n = tile * 16 + (lane & 15);
+          static_assert(NCS * SK * Mode<MODE>::KC == 4 * D, "whole K chunks per range");
+          const int ln = opaque(lane), n = tile2 * 16 + (ln & 15);
           floatx4 r[2];
-          auto keep = [&](int, const floatx4& a0, const floatx4& a1) {
+          auto keep = [&](int, const floatx4& a0, const floatx4& a1) FVAN_INLINE {
             r[0] = a0;
             r[1] = a1;
           };
-          mfma_tiles<MODE, 4 * D / SK, NRT, decltype(keep)&, Mode<MODE>::SPLIT>(
-              &sm.u.hid[0][0] + part * NCS * KC, Sm::LDH, p2 + ((size_t)tile * NC2 + (size_t)part * NCS) * 64,
-              (size_t)4 * D * D / 8, 0, 1, 1, lane, keep);
-          if (part > 0) {
+          const float bias = b2;
+          mfma_tiles<MODE, 4 * D / SK, NRT, Mode<MODE>::SPLIT, 1>(w2, &sm.u.hid[0][0] + part2 * NCS * Mode<MODE>::KC,
+                                                               Sm::LDH, 0, 1, 1, opaque(lane), keep, ahead);
+          if (part2 > 0) {
 #pragma unroll
             for (int ri = 0; ri < 4 * NRT; ++ri)
-              sm.kpart[part - 1][16 * (ri >> 2) + 4 * (lane >> 4) + (ri & 3)][n] = r[ri >> 2][ri & 3];
+              sm.kpart[part2 - 1][16 * (ri >> 2) + 4 * (ln >> 4) + (ri & 3)][n] = r[ri >> 2][ri & 3];
           }
           __syncthreads();
-          if (part == 0) {
-            const float bias = lp[U.o_ffn2_b + n];
+          if (part2 == 0) {
 #pragma unroll
             for (int ri = 0; ri < 4 * NRT; ++ri) {
-              const int row = 16 * (ri >> 2) + 4 * (lane >> 4) + (ri & 3);
+              const int row = 16 * (ri >> 2) + 4 * (ln >> 4) + (ri & 3);
               float v = r[ri >> 2][ri & 3];
 #pragma unroll
               for (int q = 0; q < Sm::KP; ++q) v += sm.kpart[q][row][n];
@@ -593,14 +826,12 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
       }
     } else {
       if (hm < KM) {
-        const float* hw = theta + U.head_w;
         float z0 = 0.f, z1 = 0.f;
 #pragma unroll
         for (int i = 0; i < D / 16; ++i) {
-          const int k = hpart + 16 * i;
-          const float x = sm.h[hm][k];
-          z0 += x * hw[k];
-          z1 += x * hw[D + k];
+          const float x = sm.h[hm][hpart + 16 * i];
+          z0 += x * hw0[i];
+          z1 += x * hw1[i];
         }
         z0 = reduce16(z0);
         z1 = reduce16(z1);
@@ -610,7 +841,7 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
                                           U.seed_lo, U.seed_hi);
             ur[0] = u24(w.x); ur[1] = u24(w.y); ur[2] = u24(w.z); ur[3] = u24(w.w);
           }
-          const float d = (z1 + theta[U.head_b + 1]) - (z0 + theta[U.head_b]);
+          const float d = (z1 + hb1) - (z0 + hb0);
           const float e = expf(-fabsf(d));
           const float pplus = d >= 0.f ? 1.0f / (1.0f + e) : e / (1.0f + e);
           const float u = ur[t & 3];

@@ -13,6 +13,24 @@
 
 namespace fvan {
 
+// Offsets (in floats) of a layer's tensors relative to its base, by d_model.
+struct LayerOffsets {
+  int64_t ln1_g, ln1_b, qkv_w, qkv_b, ln2_g, ln2_b, ffn1_w, ffn1_b, ffn2_w, ffn2_b, stride;
+};
+constexpr LayerOffsets layer_offsets(int64_t d) {
+  return LayerOffsets{0,
+                      d,
+                      2 * d,
+                      2 * d + 3 * d * d,
+                      5 * d + 3 * d * d,
+                      6 * d + 3 * d * d,
+                      7 * d + 3 * d * d,
+                      7 * d + 7 * d * d,
+                      11 * d + 7 * d * d,
+                      11 * d + 11 * d * d,
+                      12 * d + 11 * d * d};
+}
+
 // Offsets (in floats) of the tensors inside the flat FP32 parameter vector.
 struct ParamOffsets {
   int64_t tok, pos, layer0, layer_stride, head_w, head_b, total;
@@ -37,6 +55,11 @@ struct PackOffsets {
   size_t total;
 };
 PackOffsets pack_offsets(const fvan_model_config& c);
+// Bytes of a layer's packs by d_model (FP32, or a split pack's BF16 hi and lo: four
+// bytes per weight in both modes), in the order above.
+constexpr int64_t pack_layer_bytes(int64_t d) { return 22 * d * d * 4; }
+constexpr int64_t pack_ffn1_offset(int64_t d) { return 3 * d * d * 4; }
+constexpr int64_t pack_ffn2_offset(int64_t d) { return 7 * d * d * 4; }
 
 // Bytes per K/V cache element and per packed weight (FP32, or a split pack's
 // BF16 hi and lo).
@@ -71,12 +94,10 @@ struct DecodeUnit {
   int8_t* spins;       // [B][N]
   float* logq;         // [B]
   int32_t N, W, P, R, S, B, n_layers, tile0, n_tiles;
+  int32_t tile;        // samples per workgroup
   int32_t pos_off;     // offset of pos_emb in theta; tok_emb is at 0
-  int64_t layer0, layer_stride, head_w, head_b;
+  int64_t layer0, head_w, head_b;
   uint32_t seed_lo, seed_hi, stream_lo, stream_hi;
-  // per-layer relative offsets
-  int32_t o_ln1_g, o_ln1_b, o_qkv_b, o_ln2_g, o_ln2_b, o_ffn1_b, o_ffn2_b;
-  int64_t p_qkv, p_ffn1, p_ffn2, p_layer_stride;   // pack byte offsets
   int32_t d_token;
   int32_t vocab;       // 2: spins; > 2: patch tokens (uint8 written to `spins`)
 };
@@ -85,7 +106,7 @@ struct DecodeUnit {
 struct DecodeShape {
   int d_model, precision, d_head;
   bool tokens;         // vocab-way head and token draw
-  int tile;            // samples per workgroup: 32, or 16 where decode_has_tile16
+  int tile;            // samples per workgroup: 4, 8, 16 or 32 (up to 16 on 16-row tiles where decode_has_tile16)
 };
 inline DecodeShape decode_shape(const fvan_model_config& c, int tile = 32) {
   return DecodeShape{c.d_model, c.precision, c.d_model / c.n_heads, c.vocab > 2, tile};

@@ -182,6 +182,7 @@ static hipError_t group_set_tile(fvan_group* g, int tile) {
   for (auto& d : g->host_table) {
     d.tile0 = t0;
     d.n_tiles = (d.B + tile - 1) / tile;
+    d.tile = tile;
     t0 += d.n_tiles;
   }
   g->shape.tile = tile;

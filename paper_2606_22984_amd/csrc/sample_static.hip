@@ -72,7 +72,7 @@ extern "C" int fvan_sample_noalloc(fvan_model* m, int32_t batch, uint64_t seed, 
   void* kv = nullptr;
   if (int rc = scratch_address(dev, &kv)) return rc;
   DecodeShape sh = decode_shape(m->cfg);
-  sh.tile = sample_tile(m, sh, batch);
+  sh.tile = sample_tile(m, batch);
   DecodeUnit u = make_decode_unit(m, batch, seed, stream_id, spins, log_q, kv, 0, sh.tile);
   FVAN_HIP(launch_decode_single(sh, u, u.n_tiles, (hipStream_t)stream));
   FVAN_HIP(check_finite(m, log_q, batch, (hipStream_t)stream));

@@ -248,3 +248,24 @@ def test_energy_dense_spins_other_than_pm1():
     x, J = s.astype(np.float64), inst.dense.astype(np.float32).astype(np.float64)
     ref = -0.5 * ((x @ J) * x).sum(1)
     assert np.max(np.abs(E - ref)) / n <= 1e-5
+
+
+@pytest.mark.parametrize("prec", ALL_PRECISIONS)
+@pytest.mark.parametrize("d,dh,vocab", [(32, 16, 2), (64, 16, 2), (128, 16, 2), (64, 32, 2), (128, 64, 256)])
+def test_samples_do_not_depend_on_the_batch(d, dh, vocab, prec):
+    """The samples a workgroup owns (4, 8, 16 or 32) go by the batch; sample b is the same bits in every batch.
+    37 visible keys: more than one K/V batch per sample at every width; ragged last workgroups."""
+    cfg = ModelConfig(45, d, 2, d // dh, d_token=2 if vocab == 2 else 8, vocab=vocab, window=20, prefix=16)
+    batches = (3, 37, 1029, 2051, 4099, 8200)
+    m = fv.Model(cfg, batches[-1], prec, init_params(cfg, 3, "random"), workspaces=fv.WS_SAMPLER)
+    ref = None
+    for B in batches:
+        s, lq = (m.sample if vocab == 2 else m.sample_tokens)(B, 11, 2)
+        n = min(B, 37)
+        if B == 37:
+            ref = (s.clone(), lq.clone())
+        elif ref is not None:
+            assert torch.equal(s[:n], ref[0][:n]) and torch.equal(lq[:n], ref[1][:n]), B
+            if B > 1029:
+                assert torch.equal(s[:1029], last[0][:1029]) and torch.equal(lq[:1029], last[1][:1029]), B
+        last = (s.clone(), lq.clone())
