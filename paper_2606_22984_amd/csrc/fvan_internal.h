@@ -169,6 +169,7 @@ hipError_t launch_newton_schulz(const float* M, float* O, int rows, int cols, in
 // scratch (16-byte aligned): n_layers * 3 * (128^2 + 64) floats, used for d_model 128.
 hipError_t launch_muon(const fvan_model_config& c, float* theta, float* grads, float* m, float* v, int64_t n,
                        const fvan_muon& o, int64_t step, float* scratch, hipStream_t s);
+// scratch: 64 doubles (may be NULL: one workgroup).
 hipError_t launch_grad_norm(const float* g, int64_t n, double* out, double* scratch, hipStream_t s);
 hipError_t launch_mean_energy(int32_t batch, int32_t n, int is_int, const void* energy, double* out,
                               hipStream_t s);

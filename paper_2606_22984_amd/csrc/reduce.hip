@@ -83,6 +83,30 @@ __global__ __launch_bounds__(kRThreads) void sumsq_kernel(const float* __restric
   if (threadIdx.x == 0) *out = sqrt(tot);
 }
 
+// The gradient norm of a large model in two launches: kNormBlocks workgroups sum the
+// squares of interleaved elements, one adds their sums (one workgroup alone is bound
+// by the latency of its own loads: 106 us for 0.5M parameters, under 10 us now).
+constexpr int kNormBlocks = 64;
+__global__ __launch_bounds__(256) void sumsq_part_kernel(const float* __restrict__ g, int64_t n,
+                                                         double* __restrict__ part) {
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)kNormBlocks * 256)
+    s += (double)g[i] * (double)g[i];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+__global__ __launch_bounds__(64) void sumsq_final_kernel(const double* __restrict__ part, double* __restrict__ out) {
+  double s = part[threadIdx.x];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if (threadIdx.x == 0) *out = sqrt(s);
+}
+
 hipError_t launch_free_energy(int32_t batch, int32_t n, double beta, int is_int, const void* energy,
                               const float* logq, double* stats, hipStream_t s) {
   hipLaunchKernelGGL(free_energy_kernel, dim3(1), dim3(kRThreads), 0, s, batch, n, beta, is_int, energy, logq, stats);
@@ -102,7 +126,12 @@ hipError_t launch_mean_energy(int32_t batch, int32_t n, int is_int, const void* 
   return hipGetLastError();
 }
 
-hipError_t launch_grad_norm(const float* g, int64_t n, double* out, double* /*scratch*/, hipStream_t s) {
+hipError_t launch_grad_norm(const float* g, int64_t n, double* out, double* scratch, hipStream_t s) {
+  if (scratch && n > 65536) {
+    hipLaunchKernelGGL(sumsq_part_kernel, dim3(kNormBlocks), dim3(256), 0, s, g, n, scratch);
+    hipLaunchKernelGGL(sumsq_final_kernel, dim3(1), dim3(64), 0, s, (const double*)scratch, out);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(sumsq_kernel, dim3(1), dim3(kRThreads), 0, s, g, n, out);
   return hipGetLastError();
 }

@@ -126,7 +126,7 @@ static int train_step_gradient(fvan_model* m, const fvan_couplings* c, double be
   FVAN_HIP(launch_mean_energy(batch, m->cfg.n_spins, is_int, m->ts_energy, stats + 2, s));
   FVAN_HIP(launch_reinforce(batch, beta, is_int, m->ts_energy, m->ts_logq, m->ts_w, nullptr, s));
   if ((rc = fvan_log_prob_backward(m, batch, m->ts_spins, m->ts_w, stream))) return rc;
-  FVAN_HIP(launch_grad_norm(m->grads, m->n_params, stats + 3, nullptr, s));
+  FVAN_HIP(launch_grad_norm(m->grads, m->n_params, stats + 3, m->ts_dbl, s));
   return FVAN_OK;
 }
 
@@ -168,7 +168,7 @@ int fvan_train_step_distill(fvan_model* m, const fvan_couplings* c, const fvan_l
   if ((rc = fvan_log_prob(m, batch, m->ts_spins, m->ts_logq, stream))) return rc;
   FVAN_HIP(launch_reinforce(batch, beta, is_int, m->ts_energy, m->ts_logq, m->ts_w, nullptr, s, w));
   if ((rc = fvan_log_prob_backward(m, batch, m->ts_spins, m->ts_w, stream))) return rc;
-  FVAN_HIP(launch_grad_norm(m->grads, m->n_params, stats + 3, nullptr, s));
+  FVAN_HIP(launch_grad_norm(m->grads, m->n_params, stats + 3, m->ts_dbl, s));
   if ((rc = fvan_muon_step(m, opt, (int64_t)step, stream))) return rc;
   return finish_step(m, stats, s);
 }
@@ -211,7 +211,7 @@ int fvan_train_step_tokens(fvan_model* m, const fvan_couplings* c, const int32_t
   FVAN_HIP(launch_mean_energy(batch, n, is_int, m->ts_energy, stats + 2, s));
   FVAN_HIP(launch_reinforce(batch, beta, is_int, m->ts_energy, m->ts_logq, m->ts_w, nullptr, s));
   if ((rc = fvan_log_prob_tokens_backward(m, batch, tok, m->ts_w, stream))) return rc;
-  FVAN_HIP(launch_grad_norm(m->grads, m->n_params, stats + 3, nullptr, s));
+  FVAN_HIP(launch_grad_norm(m->grads, m->n_params, stats + 3, m->ts_dbl, s));
   if ((rc = fvan_muon_step(m, opt, (int64_t)step, stream))) return rc;
   return finish_step(m, stats, s);
 }

@@ -228,3 +228,18 @@ def test_backward_on_a_caller_stream_matches_default_stream(prec):
     torch.cuda.synchronize()
     say(f"caller-stream backward, precision {prec}")
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("batch", [1, 5, 4096, 4112])
+def test_backward_at_the_edges_of_the_partial_sums(batch):
+    """Gradient of batches whose LayerNorm, head and embedding partial sums take the one-launch reduction
+    (up to 512 tiles of 128 rows, 512 samples), its last size, and the two-launch one."""
+    cfg = ModelConfig(16, 32, 1, 2).with_mask(4, 5)
+    m, theta = make_model(cfg, batch, FP32, seed=6)
+    spins = random_spins(batch, 16, 8)
+    w = np.random.default_rng(1).standard_normal(batch) / batch
+    m.grads.zero_()
+    m.log_prob_backward(torch.as_tensor(spins, device="cuda"), torch.as_tensor(w.astype(np.float32), device="cuda"))
+    torch.cuda.synchronize()
+    ref = estimator.grad_surrogate(theta, cfg, spins, w.astype(np.float32).astype(np.float64))
+    assert _rel(to_np(m.grads).astype(np.float64), ref) <= GRAD_TOL[FP32]
