@@ -37,12 +37,53 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v;
 }
 
-// The DH/4 elements of a lane's slice of row r, head h, from a [rows][stride] array.
+// The DH/4 elements of a lane's slice of a row (16-byte aligned), as floats.
 template <int Q4, typename T>
 __device__ __forceinline__ void load_slice(const T* __restrict__ p, float* out) {
 #pragma unroll
-  for (int i = 0; i < Q4; ++i) out[i] = to_f(p[i]);
+  for (int i = 0; i < Q4; i += Chunk<T>::N) {
+    Chunk<T> c;
+    c.load(p + i);
+#pragma unroll
+    for (int e = 0; e < Chunk<T>::N; ++e) out[i + e] = c.v[e];
+  }
 }
+template <int Q4>
+__device__ __forceinline__ void store_slice(float* __restrict__ p, const float* v) {
+#pragma unroll
+  for (int i = 0; i < Q4; i += 4) *reinterpret_cast<float4*>(p + i) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+}
+
+// n rows of DH elements into dst, 16 bytes per load; row(i) is the address of row i.
+template <int DH, typename T, typename Row>
+__device__ __forceinline__ void stage_rows(float (*dst)[DH + 4], int n, Row&& row) {
+  constexpr int VE = Chunk<T>::N, CH = DH / VE;              // elements per load, loads per row
+  constexpr int NLD = kGenStage * CH / kGenThreads;
+  static_assert(kGenStage * CH % kGenThreads == 0, "whole rounds of loads");
+  Chunk<T> c[NLD];
+#pragma unroll
+  for (int u = 0; u < NLD; ++u) {
+    const int idx = threadIdx.x + kGenThreads * u, r = idx / CH;
+    c[u].load(row(min(r, n - 1)) + (idx % CH) * VE);
+  }
+#pragma unroll
+  for (int u = 0; u < NLD; ++u) {
+    const int idx = threadIdx.x + kGenThreads * u, r = idx / CH;
+    if (r < n) store_slice<VE>(&dst[r][(idx % CH) * VE], c[u].v);
+  }
+}
+
+// The virtual keys (KeyRange order) that a query of the wave's tw0 .. tw0 + 15 sees:
+// [0, a1) and [b0, b1).
+struct WaveKeys {
+  int a1, b0, b1;
+  __device__ WaveKeys(const KeyRange& kr, int tw0, int N, int W) {
+    const int tw1 = min(tw0 + 15, N - 1);
+    a1 = tw0 < N ? min(kr.pend, tw1 + 1) : 0;
+    b0 = kr.pend + max(0, tw0 - W - kr.bstart);
+    b1 = tw0 < N ? kr.pend + tw1 - kr.bstart + 1 : 0;
+  }
+};
 
 // ---------------------------------------------------------------- forward
 // One workgroup = (64 queries, head, sample).
@@ -70,18 +111,18 @@ __global__ __launch_bounds__(kGenThreads) void attn_fwd_gen(const KT* __restrict
   }
   const KeyRange kr(t0, t1, W, P);
   const QueryVis vis(kr, tq, W, qok);
+  const WaveKeys wk(kr, t0 + 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), N, W);
   float mx = -INFINITY, l = 0.f;
   for (int v0 = 0; v0 < kr.nk; v0 += kGenStage) {
     const int nv = min(kGenStage, kr.nk - v0);
     __syncthreads();
-    for (int idx = threadIdx.x; idx < nv * DH; idx += kGenThreads) {
-      const int key = idx / DH, d = idx % DH;
-      const KT* kp = QKV + (rowbase + kr.pos(v0 + key)) * 3 * D + D + h * DH + d;
-      Ks[key][d] = to_f(kp[0]);
-      Vs[key][d] = to_f(kp[D]);
-    }
+    auto krow = [&](int key) { return QKV + (rowbase + kr.pos(v0 + key)) * 3 * D + D + h * DH; };
+    stage_rows<DH, KT>(Ks, nv, krow);
+    stage_rows<DH, KT>(Vs, nv, [&](int key) { return krow(key) + D; });
     __syncthreads();
     for (int k0 = 0; k0 < nv; k0 += 16) {
+      const int vb = v0 + k0;
+      if ((vb >= wk.a1) & ((vb + 16 <= wk.b0) | (vb >= wk.b1))) continue;   // no query of the wave sees these keys
       float s[16];
       float mnew = mx;
 #pragma unroll
@@ -114,21 +155,24 @@ __global__ __launch_bounds__(kGenThreads) void attn_fwd_gen(const KT* __restrict
   if (qok) {
     const int64_t r = rowbase + tq;
     const float inv = 1.0f / l;
+    float x[Q4];
+    load_slice<Q4>(X + r * D + c0, x);
 #pragma unroll
-    for (int i = 0; i < Q4; ++i) XM[r * D + c0 + i] = X[r * D + c0 + i] + o[i] * inv;
+    for (int i = 0; i < Q4; ++i) x[i] = x[i] + o[i] * inv;
+    store_slice<Q4>(XM + r * D + c0, x);
     if (part == 0) LSE[r * H + h] = mx + __log2f(l);
   }
 }
 
 // ---------------------------------------------------------------- backward: dQ
 // One workgroup = (64 queries, head, sample).  O is recovered as XM - X.
-template <typename KT, typename AT, int DH>
+template <typename KT, int DH>
 __global__ __launch_bounds__(kGenThreads) void attn_bwd_dq_gen(const KT* __restrict__ QKV, const float* __restrict__ X,
                                                                const float* __restrict__ XM,
                                                                const float* __restrict__ dO,
                                                                const float* __restrict__ LSE,
-                                                               float* __restrict__ DELTA, AT* __restrict__ dQKV,
-                                                               AT* __restrict__ T, int64_t ldT, int N, int D, int H,
+                                                               float* __restrict__ DELTA, float* __restrict__ dQKV,
+                                                               float* __restrict__ T, int64_t ldT, int N, int D, int H,
                                                                int W, int P) {
   constexpr int Q4 = DH / 4;
   __shared__ __align__(16) float Ks[kGenStage][DH + 4];
@@ -146,12 +190,15 @@ __global__ __launch_bounds__(kGenThreads) void attn_bwd_dq_gen(const KT* __restr
 #pragma unroll
   for (int i = 0; i < Q4; ++i) { q[i] = 0.f; g[i] = 0.f; dq[i] = 0.f; }
   if (qok) {
+    float xm[Q4], x[Q4];
     load_slice<Q4>(QKV + r * 3 * D + c0, q);
+    load_slice<Q4>(dO + r * D + c0, g);
+    load_slice<Q4>(XM + r * D + c0, xm);
+    load_slice<Q4>(X + r * D + c0, x);
 #pragma unroll
     for (int i = 0; i < Q4; ++i) {
       q[i] *= gen_scale_log2<DH>();
-      g[i] = dO[r * D + c0 + i];
-      delta += g[i] * (XM[r * D + c0 + i] - X[r * D + c0 + i]);
+      delta += g[i] * (xm[i] - x[i]);
     }
     lse = LSE[r * H + h];
   }
@@ -159,17 +206,17 @@ __global__ __launch_bounds__(kGenThreads) void attn_bwd_dq_gen(const KT* __restr
   if (qok && part == 0) DELTA[r * H + h] = delta;
   const KeyRange kr(t0, t1, W, P);
   const QueryVis vis(kr, tq, W, qok);
+  const WaveKeys wk(kr, t0 + 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), N, W);
   for (int v0 = 0; v0 < kr.nk; v0 += kGenStage) {
     const int nv = min(kGenStage, kr.nk - v0);
     __syncthreads();
-    for (int idx = threadIdx.x; idx < nv * DH; idx += kGenThreads) {
-      const int key = idx / DH, d = idx % DH;
-      const KT* kp = QKV + (rowbase + kr.pos(v0 + key)) * 3 * D + D + h * DH + d;
-      Ks[key][d] = to_f(kp[0]);
-      Vs[key][d] = to_f(kp[D]);
-    }
+    auto krow = [&](int key) { return QKV + (rowbase + kr.pos(v0 + key)) * 3 * D + D + h * DH; };
+    stage_rows<DH, KT>(Ks, nv, krow);
+    stage_rows<DH, KT>(Vs, nv, [&](int key) { return krow(key) + D; });
     __syncthreads();
-    for (int key = 0; key < nv; ++key) {
+    // the wave's visible keys of this block, in order: [0, a1) then [b0, b1)
+    const int na = max(0, min(wk.a1 - v0, nv)), k1 = max(na, wk.b0 - v0), ke = min(wk.b1 - v0, nv);
+    for (int it2 = k1 < ke ? na + ke - k1 : na, key = na > 0 ? 0 : k1; it2 > 0; --it2, key = key + 1 == na ? k1 : key + 1) {
       float s = 0.f, dp = 0.f;
 #pragma unroll
       for (int i = 0; i < Q4; ++i) {
@@ -186,23 +233,22 @@ __global__ __launch_bounds__(kGenThreads) void attn_bwd_dq_gen(const KT* __restr
   }
   if (qok) {
 #pragma unroll
-    for (int i = 0; i < Q4; ++i) {
-      const AT v = from_f<AT>(dq[i] * gen_inv_sqrt<DH>());
-      dQKV[r * 3 * D + c0 + i] = v;
-      T[(int64_t)(c0 + i) * ldT + r] = v;
-    }
+    for (int i = 0; i < Q4; ++i) dq[i] *= gen_inv_sqrt<DH>();
+    store_slice<Q4>(dQKV + r * 3 * D + c0, dq);
+#pragma unroll
+    for (int i = 0; i < Q4; ++i) T[(int64_t)(c0 + i) * ldT + r] = dq[i];
   }
 }
 
 // ---------------------------------------------------------------- backward: dK, dV
 // One workgroup = (64 keys, head, sample).  The queries that see key j are
 // i >= j with i - j <= W, or every i >= j when j < P.
-template <typename KT, typename AT, int DH>
+template <typename KT, int DH>
 __global__ __launch_bounds__(kGenThreads) void attn_bwd_dkv_gen(const KT* __restrict__ QKV,
                                                                 const float* __restrict__ dO,
                                                                 const float* __restrict__ LSE,
                                                                 const float* __restrict__ DELTA,
-                                                                AT* __restrict__ dQKV, AT* __restrict__ T, int64_t ldT,
+                                                                float* __restrict__ dQKV, float* __restrict__ T, int64_t ldT,
                                                                 int N, int D, int H, int W, int P) {
   constexpr int Q4 = DH / 4;
   __shared__ __align__(16) float Qs[kGenStage][DH + 4];
@@ -224,21 +270,20 @@ __global__ __launch_bounds__(kGenThreads) void attn_bwd_dkv_gen(const KT* __rest
   }
   // queries of the tile's keys: [j0, i_end)
   const int i_end = j0 < P ? N : min(N, j1 - 1 + W + 1);
+  // of them, those that see one of the wave's keys jw0 .. jw0 + 15: [jw0, iw_end)
+  const int jw0 = j0 + 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int iw_end = jw0 >= N ? jw0 : (jw0 < P ? i_end : min(i_end, min(N - 1, jw0 + 15) + W + 1));
   for (int i0 = j0; i0 < i_end; i0 += kGenStage) {
     const int nq = min(kGenStage, i_end - i0);
     __syncthreads();
-    for (int idx = threadIdx.x; idx < nq * DH; idx += kGenThreads) {
-      const int qi = idx / DH, d = idx % DH;
-      const int64_t rq = rowbase + i0 + qi;
-      Qs[qi][d] = to_f(QKV[rq * 3 * D + h * DH + d]);
-      Gs[qi][d] = dO[rq * D + h * DH + d];
-    }
+    stage_rows<DH, KT>(Qs, nq, [&](int qi) { return QKV + (rowbase + i0 + qi) * 3 * D + h * DH; });
+    stage_rows<DH, float>(Gs, nq, [&](int qi) { return dO + (rowbase + i0 + qi) * D + h * DH; });
     for (int qi = threadIdx.x; qi < nq; qi += kGenThreads) {
       Ls[qi] = LSE[(rowbase + i0 + qi) * H + h];
       Ds[qi] = DELTA[(rowbase + i0 + qi) * H + h];
     }
     __syncthreads();
-    for (int qi = 0; qi < nq; ++qi) {
+    for (int qi = max(0, jw0 - i0); qi < min(nq, iw_end - i0); ++qi) {
       float s = 0.f, dp = 0.f;
 #pragma unroll
       for (int i = 0; i < Q4; ++i) {
@@ -259,12 +304,13 @@ __global__ __launch_bounds__(kGenThreads) void attn_bwd_dkv_gen(const KT* __rest
   if (kok) {
     const int64_t r = rowbase + j;
 #pragma unroll
+    for (int i = 0; i < Q4; ++i) dk[i] *= gen_inv_sqrt<DH>();
+    store_slice<Q4>(dQKV + r * 3 * D + D + c0, dk);
+    store_slice<Q4>(dQKV + r * 3 * D + 2 * D + c0, dv);
+#pragma unroll
     for (int i = 0; i < Q4; ++i) {
-      const AT kv = from_f<AT>(dk[i] * gen_inv_sqrt<DH>()), vv = from_f<AT>(dv[i]);
-      dQKV[r * 3 * D + D + c0 + i] = kv;
-      dQKV[r * 3 * D + 2 * D + c0 + i] = vv;
-      T[(int64_t)(D + c0 + i) * ldT + r] = kv;
-      T[(int64_t)(2 * D + c0 + i) * ldT + r] = vv;
+      T[(int64_t)(D + c0 + i) * ldT + r] = dk[i];
+      T[(int64_t)(2 * D + c0 + i) * ldT + r] = dv[i];
     }
   }
 }

@@ -781,17 +781,17 @@ __global__ __launch_bounds__(64) void tok_grad_vocab_kernel(const float* __restr
 
 // ---------------------------------------------------------------- driver
 // Attention backward of one layer for heads wider than 16 (attn_generic.h).
-template <typename KT, typename AT, int DH>
+template <typename KT, int DH>
 static hipError_t attn_bwd_gen(fvan_model* m, const KT* QKV, const float* X, const float* XM, const float* LSE,
                                int nsamp, hipStream_t s) {
   const fvan_model_config& c = m->cfg;
   auto& f = m->fw;
   const int N = c.n_spins, D = c.d_model, H = c.n_heads;
   const int grid = (N + kGenRows - 1) / kGenRows * H * nsamp;
-  hipLaunchKernelGGL((attn_bwd_dq_gen<KT, AT, DH>), dim3(grid), dim3(kGenThreads), 0, s, QKV, X, XM,
-                     (const float*)f.dXM, LSE, f.DELTA, (AT*)f.dQKV, (AT*)f.T_e, f.ldT, N, D, H, c.window, m->kg.P);
-  hipLaunchKernelGGL((attn_bwd_dkv_gen<KT, AT, DH>), dim3(grid), dim3(kGenThreads), 0, s, QKV, (const float*)f.dXM,
-                     LSE, (const float*)f.DELTA, (AT*)f.dQKV, (AT*)f.T_e, f.ldT, N, D, H, c.window, m->kg.P);
+  hipLaunchKernelGGL((attn_bwd_dq_gen<KT, DH>), dim3(grid), dim3(kGenThreads), 0, s, QKV, X, XM,
+                     (const float*)f.dXM, LSE, f.DELTA, (float*)f.dQKV, (float*)f.T_e, f.ldT, N, D, H, c.window, m->kg.P);
+  hipLaunchKernelGGL((attn_bwd_dkv_gen<KT, DH>), dim3(grid), dim3(kGenThreads), 0, s, QKV, (const float*)f.dXM,
+                     LSE, (const float*)f.DELTA, (float*)f.dQKV, (float*)f.T_e, f.ldT, N, D, H, c.window, m->kg.P);
   return hipGetLastError();
 }
 
@@ -905,10 +905,10 @@ static hipError_t backward_chunk_t(fvan_model* m, const void* seq, int nsamp, co
                            c.window, m->kg.P);
       }
     } else if (D / H == 32) {
-      if ((err = attn_bwd_gen<KT, AT, 32>(m, QKV, X, XM, LSE, nsamp, s))) return err;
+      if ((err = attn_bwd_gen<KT, 32>(m, QKV, X, XM, LSE, nsamp, s))) return err;
     } else {
       if constexpr (D >= 64)
-        if ((err = attn_bwd_gen<KT, AT, 64>(m, QKV, X, XM, LSE, nsamp, s))) return err;
+        if ((err = attn_bwd_gen<KT, 64>(m, QKV, X, XM, LSE, nsamp, s))) return err;
     }
     // ---- QKV backward: dA1 = dQKV W_qkv and the LN1 backward in one kernel, which
     // also leaves LN1(x) feature-major for the W_qkv gradient

@@ -200,3 +200,26 @@ def test_spin_model_with_wide_heads(prec, d_head):
     rel = np.linalg.norm(g - gref) / np.linalg.norm(gref)
     say(f"  gradient rel. error {rel:.2e}")
     assert rel <= GRAD_TOL[prec]
+
+
+@pytest.mark.parametrize("prec", [FP32, SPLIT])
+@pytest.mark.parametrize("n,window,prefix,dh", [(1, 0, 0, 64), (15, 3, 2, 32), (64, 63, 0, 64), (65, 10, 17, 64),
+                                                (130, 5, 40, 32), (150, 70, 0, 64)])
+def test_wide_head_attention_at_tile_edges(n, window, prefix, dh, prec):
+    """ln q and its gradient for 32- and 64-wide heads at the edges of the 16-row waves, the 64-row tiles and
+    the band / prefix seams of the masks; GRAD_TOL as for the narrow heads."""
+    cfg = ModelConfig(n, 64, 2, 64 // dh, vocab=16, d_token=8).with_mask(window, prefix)
+    m, theta = make_model(cfg, 5, prec, seed=3)
+    rng = np.random.default_rng(n)
+    tok = rng.integers(0, 16, (5, n)).astype(np.uint8)
+    w = (rng.standard_normal(5) / 5).astype(np.float32)
+    t = torch.as_tensor(tok, device="cuda")
+    lq = to_np(m.log_prob_tokens(t)).astype(np.float64)
+    m.grads.zero_()
+    m.log_prob_tokens_backward(t, torch.as_tensor(w, device="cuda"))
+    torch.cuda.synchronize()
+    ref = patch.log_q_tokens(theta, cfg, tok)
+    assert np.max(np.abs(lq - ref)) / n <= SITE_TOL[prec]
+    gr = patch.grad_surrogate_tokens(theta, cfg, tok, w.astype(np.float64))
+    g = to_np(m.grads).astype(np.float64)
+    assert np.linalg.norm(g - gr) <= GRAD_TOL[prec] * np.linalg.norm(gr)
