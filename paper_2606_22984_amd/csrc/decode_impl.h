@@ -35,6 +35,8 @@
 // with 16-wide heads) and decode_ext.hip (other head widths and token models).
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "fvan_model.h"
 
@@ -750,33 +752,47 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
 
     // ---- head, Philox draw, decision ----
     if constexpr (TOK) {
-      // logits z[m][v] = W_h[v] . h[m] + b[v]: thread (v, half) for samples 16 half .. 16 half + 15
+      // logits z[m][v] = W_h[v] . h[m] + b[v]: thread (v, half) for half of the tile's
+      // samples, up to 8 at a time.  The weights are read across the vocabulary (the FP32
+      // transpose), 8 loads in flight.  Bound by the reads of sm.h: row-wise weight reads,
+      // one cache line per lane, took 22 of the 49 us of a step of d = 128, 256 tokens and
+      // 8 samples per workgroup; now 10.  All 16 samples of a half at a time, or 16 loads
+      // in flight, spill registers and are 2 to 5 % slower over a call.
       {
         const int v = tid & (kMaxVocab - 1), half = tid / kMaxVocab;
-        if (v < U.vocab && 16 * half < KM) {
-          const float* wr = theta + U.head_w + (size_t)v * D;
-          float acc[16];
+        const int each = (nb + 1) / 2, m0 = half * each, m1 = min(nb, m0 + each);
+        const uint32_t wv = (uint32_t)(min(v, U.vocab - 1) * U.head_sv);
+        auto logits = [&](auto count) FVAN_INLINE {
+          constexpr int S = decltype(count)::value;
+          for (int mb = m0; mb < m1; mb += S) {
+            float acc[S];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+            for (int i = 0; i < S; ++i) acc[i] = 0.f;
 #pragma unroll 2
-          for (int k = 0; k < D; k += 4) {
-            const float w0 = wr[k], w1 = wr[k + 1], w2 = wr[k + 2], w3 = wr[k + 3];
+            for (int k = 0; k < D; k += 4) {
+              const float* wr = U.head + (uint32_t)(k * U.head_sk);
+              const float w0 = wr[wv], w1 = wr[wv + U.head_sk], w2 = wr[wv + 2 * U.head_sk], w3 = wr[wv + 3 * U.head_sk];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const float4 x = *reinterpret_cast<const float4*>(&sm.h[16 * half + i][k]);
-              acc[i] += w0 * x.x + w1 * x.y + w2 * x.z + w3 * x.w;
+              for (int i = 0; i < S; ++i) {
+                const float4 x = *reinterpret_cast<const float4*>(&sm.h[min(mb + i, KM - 1)][k]);
+                acc[i] += w0 * x.x + w1 * x.y + w2 * x.z + w3 * x.w;
+              }
             }
-          }
-          const float bias = theta[U.head_b + v];
+            const float bias = theta[U.head_b + min(v, U.vocab - 1)];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) sm.u.z[16 * half + i][v] = acc[i] + bias;
-        }
+            for (int i = 0; i < S; ++i)
+              if (v < U.vocab && mb + i < m1) sm.u.z[mb + i][v] = acc[i] + bias;
+          }
+        };
+        if (each <= 2) logits(std::integral_constant<int, 2>());
+        else if (each <= 4) logits(std::integral_constant<int, 4>());
+        else logits(std::integral_constant<int, 8>());
       }
       __syncthreads();
       // softmax and draw: 16 lanes per sample, lane hpart holds logits 16 hpart .. 16 hpart + 15.
       // The token is the largest k >= 1 with u < sum_{j >= k} p_j (else 0), decided as
       // u * total < sum_{j >= k} e_j with e_j = exp(z_j - max), total = sum_j e_j.
-      if (hm < KM) {
+      if (hm < nb) {
         const int V = U.vocab, v0 = 16 * hpart;
         float zl[16];
         float mx = -INFINITY;

@@ -49,8 +49,9 @@ ParamOffsets param_offsets(const fvan_model_config& c);
 struct PackOffsets {
   size_t qkv, ffn1, ffn2, qkvT, ffn1T, ffn2T, layer_stride;
   // models over patch tokens (vocab > 2): the head W_h [vocab x d] padded to vp
-  // rows (vp = vocab rounded up to 32, zero rows), and its transpose [d x vp]
-  size_t head, headT;
+  // rows (vp = vocab rounded up to 32, zero rows), its transpose [d x vp], and the
+  // transpose as plain FP32 rows of vp (headF: what the sampler's head reads)
+  size_t head, headT, headF;
   int vp;
   size_t total;
 };
@@ -99,6 +100,8 @@ struct DecodeUnit {
   int64_t layer0, head_w, head_b;
   uint32_t seed_lo, seed_hi, stream_lo, stream_hi;
   int32_t d_token;
+  const float* head;   // head weight of output v and feature k: head[v * head_sv + k * head_sk] (token models)
+  int32_t head_sv, head_sk;
   int32_t vocab;       // 2: spins; > 2: patch tokens (uint8 written to `spins`)
 };
 

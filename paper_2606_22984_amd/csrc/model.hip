@@ -255,6 +255,11 @@ DecodeUnit make_decode_unit(const fvan_model* m, int32_t batch, uint64_t seed, u
   u.stream_hi = (uint32_t)(stream_id >> 32);
   u.d_token = c.d_token;
   u.vocab = c.vocab;
+  // the FP32 transpose (coalesced over the vocabulary) where there is one
+  u.head = m->pk.vp ? reinterpret_cast<const float*>(reinterpret_cast<const char*>(m->wpack) + m->pk.headF)
+                    : m->params + m->po.head_w;
+  u.head_sv = m->pk.vp ? 1 : c.d_model;
+  u.head_sk = m->pk.vp ? m->pk.vp : 1;
   return u;
 }
 

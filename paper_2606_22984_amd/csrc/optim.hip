@@ -21,7 +21,8 @@ struct PackJob {
 };
 
 // The matrices of a model, for pack_kernel: job y < 6 n_layers is matrix y % 6 of
-// layer y / 6; the two after them are the vocab-way head and its transpose.
+// layer y / 6; the three after them are the vocab-way head, its transpose and the
+// plain FP32 transpose.
 struct PackPlan {
   const float* theta;
   char* wpack;
@@ -33,6 +34,8 @@ struct PackPlan {
 __device__ __forceinline__ PackJob pack_job(const PackPlan& p, int y) {
   const int D = p.D;
   if (y >= 6 * p.n_layers) {
+    if (y == 6 * p.n_layers + 2)
+      return PackJob{p.theta + p.head_w, p.wpack + p.pk.headF, p.pk.vp, D, 2, p.vocab};
     const bool t = y > 6 * p.n_layers;
     return PackJob{p.theta + p.head_w, p.wpack + (t ? p.pk.headT : p.pk.head), t ? D : p.pk.vp, t ? p.pk.vp : D, t,
                    p.vocab};
@@ -61,6 +64,14 @@ __global__ void pack_kernel(PackPlan plan) {
   const PackJob j = pack_job(plan, blockIdx.y);
   WT* dst = reinterpret_cast<WT*>(j.dst);
   const int total = j.rows * j.K;
+  if (j.transposed == 2) {   // dst[k][r] = src[r][k], FP32
+    float* f = reinterpret_cast<float*>(j.dst);
+    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < total; p += gridDim.x * blockDim.x) {
+      const int r = p % j.rows, k = p / j.rows;
+      f[p] = r < j.valid ? j.src[(size_t)r * j.K + k] : 0.f;
+    }
+    return;
+  }
   const int nchunk = j.K / KC;
   for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < total; p += gridDim.x * blockDim.x) {
     const int e = p % VEC;
@@ -84,7 +95,7 @@ static hipError_t pack_all(const fvan_model_config& c, const float* theta, void*
   const ParamOffsets po = param_offsets(c);
   const PackPlan plan{theta,     reinterpret_cast<char*>(wpack), po.layer0, po.layer_stride, po.qkv_w, po.ffn1_w,
                       po.ffn2_w, po.head_w,                       pack_offsets(c), c.d_model, c.n_layers, c.vocab};
-  const int jobs = 6 * c.n_layers + (plan.pk.vp ? 2 : 0);
+  const int jobs = 6 * c.n_layers + (plan.pk.vp ? 3 : 0);
   if (jobs == 0) return hipSuccess;
   const int largest = std::max(4 * c.d_model, plan.pk.vp) * c.d_model;
   hipLaunchKernelGGL((pack_kernel<MODE>), dim3((largest + 255) / 256, jobs), dim3(256), 0, s, plan);

@@ -269,3 +269,16 @@ def test_samples_do_not_depend_on_the_batch(d, dh, vocab, prec):
             if B > 1029:
                 assert torch.equal(s[:1029], last[0][:1029]) and torch.equal(lq[:1029], last[1][:1029]), B
         last = (s.clone(), lq.clone())
+
+
+@pytest.mark.parametrize("vocab,batch", [(3, 1), (16, 5), (33, 37), (255, 9), (256, 4099)])
+def test_token_head_of_any_vocabulary(vocab, batch):
+    """The sampler's ln q against the teacher-forced pass of the same tokens: vocabularies off the
+    padding's multiple of 32, and 1 to 16 samples per half workgroup.  Both are FP32 sums of at most
+    64 terms per logit: a site's ln q agrees to a few hundred ulp."""
+    cfg = ModelConfig(9, 64, 2, 4, d_token=8, vocab=vocab, window=5, prefix=2)
+    m = fv.Model(cfg, batch, FP32, init_params(cfg, 4, "random"))
+    tok, lq = m.sample_tokens(batch, 21, 1)
+    assert int(tok.max()) < vocab
+    ref = to_np(m.log_prob_tokens(tok)).astype(np.float64)
+    assert np.max(np.abs(to_np(lq).astype(np.float64) - ref)) / cfg.n_spins <= 5e-5
