@@ -75,6 +75,19 @@ __device__ __forceinline__ floatx4 mma_dup_hl(const SplitDup& a, const SplitBf16
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l0, b8, acc, 0, 0, 0);
 }
 
+// Four consecutive rows of a feature-major output (dword-aligned: a sample's first row
+// need not be a multiple of four), rows past `live` left alone.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_rows4(float* __restrict__ dst, const floatx4& v, int live) {
+  if (live >= 4) {
+    *reinterpret_cast<float4u*>(dst) = float4u{v[0], v[1], v[2], v[3]};
+  } else {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (i < live) dst[i] = v[i];
+  }
+}
+
 constexpr float kMaxFloor = -1e30f;   // finite start of the running maximum (unscaled score units)
 constexpr int kKhStride = 20;         // K rows in LDS: 16 halves + 4 (40 bytes)
 constexpr int kVtStride = kKeyChunk + 8;   // V^T rows in LDS: one per dim
@@ -121,7 +134,52 @@ static __global__ __launch_bounds__(kFwdThreads) void attn_fwd_f16(const _Float1
   fetch(0);
   float mx = kMaxFloor, l = 0.f;
   floatx4 o = {0.f, 0.f, 0.f, 0.f};        // O^T[dim 4g+i][query c]
-  for (int v0 = 0; v0 < kr.nk; v0 += kKeyChunk) {
+  int v0 = 0;
+  // the 64 keys from kt0 of the staged chunk, with the tile classes cls(0..3)
+  auto block = [&](int kt0, auto&& cls) FVAN_INLINE {
+    float s[16];
+    float bmax = kMaxFloor;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const half4_t ka = *reinterpret_cast<const half4_t*>(&Kh[kt0 + 16 * u + c][4 * g]);
+      const floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x16f16(ka, qh, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[4 * u + i] = acc[i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (cls(u) == 2) continue;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[4 * u + i] = vis(v0 + kt0 + 16 * u + 4 * g + i) ? s[4 * u + i] : -INFINITY;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bmax = fmaxf(bmax, s[i]);
+    bmax = max_xor32(max_xor16(bmax));
+    const float mn = fmaxf(mx, bmax);
+    const float ms = mn * kScaleLog2;
+    const float corr = __builtin_amdgcn_exp2f((mx - mn) * kScaleLog2);
+    float ps = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], kScaleLog2, -ms));   // masked: exp2(-inf) = 0
+      ps += s[i];
+    }
+    ps = sum_xor32(sum_xor16(ps));
+    l = l * corr + ps;
+    mx = mn;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] *= corr;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (cls(u) == 0) continue;
+      // A = V^T[dim c][keys 4g..+3 of the tile] twice along k, B = [P_hi ; P_lo] of those keys, query c
+      const half4_t va = *reinterpret_cast<const half4_t*>(&Vt[c][kt0 + 16 * u + 4 * g]);
+      const half8_t a8 = __builtin_shufflevector(va, va, 0, 1, 2, 3, 0, 1, 2, 3);
+      o = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, split_f16x4(s[4 * u], s[4 * u + 1], s[4 * u + 2], s[4 * u + 3]),
+                                                o, 0, 0, 0);
+    }
+  };
+  for (; v0 < kr.nk; v0 += kKeyChunk) {
     const int nv = min(kKeyChunk, kr.nk - v0);
     __syncthreads();                        // the previous chunk's reads are done
     {
@@ -138,6 +196,19 @@ static __global__ __launch_bounds__(kFwdThreads) void attn_fwd_f16(const _Float1
     __syncthreads();
     if (v0 + kKeyChunk < kr.nk) fetch(v0 + kKeyChunk);
     for (int kt0 = 0; kt0 < nv; kt0 += 64) {
+      // Most blocks have four full tiles: one test of the block's ends, straight-line
+      // code, and the four score products in flight together.  Tile classes with a branch
+      // each around their product cost 150 scalar instructions a block, in every block
+      // (512 samples of 512 spins, 8 heads, full causal: 291 -> 249 us a layer, bound by the
+      // vector instructions of the softmax and the FP16 split).
+      const int vb0 = v0 + kt0, p00 = kr.bstart + (vb0 - kr.pend);
+      const bool all = (kt0 + 64 <= nv) & (vb0 + 64 <= kr.pend
+                                               ? vb0 + 63 <= tw0                                    // prefix keys j <= t
+                                               : (vb0 >= kr.pend) & (p00 + 63 <= tw0) & (tw1 - p00 <= W));   // band
+      if (all) {
+        block(kt0, [](int) FVAN_INLINE { return 2; });
+        continue;
+      }
       // class of each 16-key tile for this wave: 0 empty, 1 partial, 2 full
       int cls[4];
 #pragma unroll
@@ -156,53 +227,7 @@ static __global__ __launch_bounds__(kFwdThreads) void attn_fwd_f16(const _Float1
         cls[u] = any ? (full ? 2 : 1) : 0;
       }
       if ((cls[0] | cls[1] | cls[2] | cls[3]) == 0) continue;
-      float s[16];
-      float bmax = kMaxFloor;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int kl = kt0 + 16 * u;
-        if (cls[u] == 0) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) s[4 * u + i] = -INFINITY;
-          continue;
-        }
-        const half4_t ka = *reinterpret_cast<const half4_t*>(&Kh[kl + c][4 * g]);
-        const floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x16f16(ka, qh, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        if (cls[u] == 2) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) s[4 * u + i] = acc[i];
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) s[4 * u + i] = vis(v0 + kl + 4 * g + i) ? acc[i] : -INFINITY;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bmax = fmaxf(bmax, s[4 * u + i]);
-      }
-      bmax = max_xor32(max_xor16(bmax));
-      const float mn = fmaxf(mx, bmax);
-      const float ms = mn * kScaleLog2;
-      const float corr = __builtin_amdgcn_exp2f((mx - mn) * kScaleLog2);
-      float ps = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], kScaleLog2, -ms));   // masked: exp2(-inf) = 0
-        ps += s[i];
-      }
-      ps = sum_xor32(sum_xor16(ps));
-      l = l * corr + ps;
-      mx = mn;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] *= corr;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (cls[u] == 0) continue;
-        const int kl = kt0 + 16 * u;
-        // A = V^T[dim c][keys kl+4g..+3] twice along k, B = [P_hi ; P_lo] of those keys, query c
-        const half4_t va = *reinterpret_cast<const half4_t*>(&Vt[c][kl + 4 * g]);
-        const half8_t a8 = __builtin_shufflevector(va, va, 0, 1, 2, 3, 0, 1, 2, 3);
-        o = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, split_f16x4(s[4 * u], s[4 * u + 1], s[4 * u + 2], s[4 * u + 3]),
-                                                  o, 0, 0, 0);
-      }
+      block(kt0, [&](int u) FVAN_INLINE { return cls[u]; });
     }
   }
   if (qok) {
@@ -260,6 +285,11 @@ static __global__ __launch_bounds__(kDqThreads) void attn_bwd_dq_f16(const _Floa
   const int wa1 = tw0 < N ? min(kr.pend, tw1 + 1) : 0;
   const int wb0 = kr.pend + max(0, tw0 - W - kr.bstart);
   const int wb1 = tw0 < N ? kr.pend + tw1 - kr.bstart + 1 : 0;
+  // tiles from key v on that every query of the wave sees whole: v <= fa1 in the prefix
+  // (keys j <= t), fb0 <= v <= fb1 in the band (keys t - W <= j <= t)
+  const int fa1 = min(min(kr.pend, kr.nk) - 16, tw0 - 15);
+  const int fb0 = kr.pend + max(0, tw1 - W - kr.bstart);
+  const int fb1 = min(kr.nk - 16, kr.pend + tw0 - 15 - kr.bstart);
   const int64_t r = rowbase + tq;
   half4_t qh = {0, 0, 0, 0};
   float4 g4 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -300,15 +330,7 @@ static __global__ __launch_bounds__(kDqThreads) void attn_bwd_dq_f16(const _Floa
     for (int kb = 0; kb < nv; kb += 16) {
       const int vb = v0 + kb;
       if ((vb >= wa1) & ((vb + 16 <= wb0) | (vb >= wb1))) continue;   // no query of the wave sees these keys
-      bool full = false;
-      if (kb + 16 <= nv) {
-        if (vb + 16 <= kr.pend) {
-          full = vb + 15 <= tw0;
-        } else if (vb >= kr.pend) {
-          const int p0 = kr.bstart + (vb - kr.pend);
-          full = (p0 + 15 <= tw0) & (tw1 - p0 <= W);
-        }
-      }
+      const bool full = (vb <= fa1) | ((vb >= fb0) & (vb <= fb1));
       const half4_t ka = *reinterpret_cast<const half4_t*>(&Kh[kb + c][4 * g]);
       const floatx4 sa = __builtin_amdgcn_mfma_f32_16x16x16f16(ka, qh, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
       const floatx4 pa = mma_hl_dup(Va[kb + c][g], gB, floatx4{0.f, 0.f, 0.f, 0.f});   // dP^T[key 4g+i][query c]
@@ -327,16 +349,16 @@ static __global__ __launch_bounds__(kDqThreads) void attn_bwd_dq_f16(const _Floa
       dq = mma_dup_hl(split_dup(ds[0], ds[1], ds[2], ds[3]), Kb[c][kb / 4 + g], dq);
     }
   }
+  // rows tqo .. tqo + 3 of column c
+  const int tqo = t0 + 16 * wave + 4 * g;
+  const int64_t ro = rowbase + tqo;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tqi = t0 + 16 * wave + 4 * g + i;
-    if (tqi < N) {
-      const int64_t ri = rowbase + tqi;
-      const float v = dq[i] * 0.25f;
-      dQKV[ri * 3 * D + h * 16 + c] = v;
-      T[(int64_t)(h * 16 + c) * ldT + ri] = v;
-    }
-  }
+  for (int i = 0; i < 4; ++i) dq[i] *= 0.25f;
+  float* po = dQKV + ro * 3 * D + h * 16 + c;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (tqo + i < N) po[i * 3 * D] = dq[i];
+  store_rows4(T + (int64_t)(h * 16 + c) * ldT + ro, dq, N - tqo);
 }
 
 // ---------------------------------------------------------------- backward: dK, dV
@@ -381,6 +403,10 @@ static __global__ __launch_bounds__(kDkvThreads) void attn_bwd_dkv_f16(const _Fl
   const int qhi_w = jw0 >= N ? jw0 : (jw0 < P ? qend : min(qend, min(N - 1, jw0 + 15) + W + 1));
   // the wave's keys all lie in the prefix, or all in the band (else its tiles are partial)
   const bool wpre = jw0 + 15 < P, wband = jw0 >= P, wkeys = jw0 + 15 < N;
+  // query tiles from i on with every (query, key) pair visible: keys before every query,
+  // and within the band of every query unless all are prefix keys: flo <= i <= fhi
+  const int flo = jw0 + 15;
+  const int fhi = !wkeys ? -1 : min(qend - 16, wpre ? N : wband ? jw0 + W - 15 : -1);
   // staging roles as in the FP32 kernel: dO row tid/4, quarter tid%4; Q row tid/2,
   // dims 8 (tid & 1) .. (tid < 2 QB); LSE (tid < QB) or DELTA (QB <= tid < 2 QB)
   static_assert(QB * 4 == kDkvThreads, "dK/dV staging: one dO quarter-row per thread");
@@ -391,14 +417,24 @@ static __global__ __launch_bounds__(kDkvThreads) void attn_bwd_dkv_f16(const _Fl
   float4 graw = make_float4(0.f, 0.f, 0.f, 0.f);
   uint4 qraw = make_uint4(0u, 0u, 0u, 0u);
   float sraw = 0.f;
+  // the pointers walk from block to block: formed anew, their 64-bit products were an
+  // eighth of the kernel's vector instruction time.  With the four-row stores at the
+  // end (16 lines an instruction before, at a dword each): 1.79 -> 1.54 ms (1024 samples
+  // of 1000 spins, 8 heads, 226 visible keys), 0.66 -> 0.47 ms (34 visible keys)
+  const float* gp = dO + (rowbase + j0 + gr) * D + h * 16 + gc;
+  const _Float16* qp = QKV + (rowbase + j0 + qr) * 3 * D + h * 16 + qc;
+  const float* sp = (tid < QB ? LSE : DELTA) + (rowbase + j0 + sr) * H + h;
   auto fetch = [&](int i0) {
     const int nq = min(QB, qend - i0);
     graw = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (gr < nq) graw = *reinterpret_cast<const float4*>(dO + (rowbase + i0 + gr) * D + h * 16 + gc);
+    if (gr < nq) graw = *reinterpret_cast<const float4*>(gp);
     qraw = make_uint4(0u, 0u, 0u, 0u);
-    if (qthr & (qr < nq)) qraw = *reinterpret_cast<const uint4*>(QKV + (rowbase + i0 + qr) * 3 * D + h * 16 + qc);
+    if (qthr & (qr < nq)) qraw = *reinterpret_cast<const uint4*>(qp);
     sraw = 0.f;
-    if ((tid < 2 * QB) & (sr < nq)) sraw = (tid < QB ? LSE : DELTA)[(rowbase + i0 + sr) * H + h];
+    if ((tid < 2 * QB) & (sr < nq)) sraw = *sp;
+    gp += QB * D;
+    qp += QB * 3 * D;
+    sp += QB * H;
   };
   fetch(j0);
   floatx4 dk = {0.f, 0.f, 0.f, 0.f}, dv = {0.f, 0.f, 0.f, 0.f};   // [key 16w+4g+i][dim c]
@@ -423,12 +459,11 @@ static __global__ __launch_bounds__(kDkvThreads) void attn_bwd_dkv_f16(const _Fl
     build_b<2, QB, kDkvThreads>(Qf, Qb);
     build_b<2, QB, kDkvThreads>(Gf, Gb);
     __syncthreads();
-    for (int q0 = 0; q0 < nq; q0 += 16) {
+    // from the first query that sees a key of the wave to the last
+    const int qstop = min(nq, qhi_w - i0);
+    for (int q0 = max(0, jw0 - i0); q0 < qstop; q0 += 16) {
       const int iq0 = i0 + q0;
-      if ((iq0 + 16 <= jw0) | (iq0 >= qhi_w)) continue;   // no key of the wave sees these queries
-      // every (query, key) pair of the tile visible: keys before every query, and
-      // within the band of every query unless all are prefix keys
-      const bool full = wkeys & (iq0 + 16 <= qend) & (jw0 + 15 <= iq0) & (wpre | (wband & (iq0 + 15 - jw0 <= W)));
+      const bool full = (iq0 >= flo) & (iq0 <= fhi);
       const half4_t qa = *reinterpret_cast<const half4_t*>(&Qh[q0 + c][4 * g]);
       const floatx4 sa = __builtin_amdgcn_mfma_f32_16x16x16f16(qa, kh, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
       const floatx4 pa = mma_hl_dup(Ga[q0 + c][g], vB, floatx4{0.f, 0.f, 0.f, 0.f});   // dP[q 4g+i][key c]
@@ -448,19 +483,21 @@ static __global__ __launch_bounds__(kDkvThreads) void attn_bwd_dkv_f16(const _Fl
       dk = mma_dup_hl(split_dup(ds[0], ds[1], ds[2], ds[3]), Qb[c][q0 / 4 + g], dk);  // dK += dS^T Q
     }
   }
+  // rows jo .. jo + 3 of column c
+  const int jo = j0 + 16 * wave + 4 * g;
+  const int64_t ro = rowbase + jo;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int jj = j0 + 16 * wave + 4 * g + i;
-    if (jj < N) {
-      const int64_t rj = rowbase + jj;
-      const float kvv = dk[i] * 0.25f;
-      const float vvv = dv[i];
-      dQKV[rj * 3 * D + D + h * 16 + c] = kvv;
-      dQKV[rj * 3 * D + 2 * D + h * 16 + c] = vvv;
-      T[(int64_t)(D + h * 16 + c) * ldT + rj] = kvv;
-      T[(int64_t)(2 * D + h * 16 + c) * ldT + rj] = vvv;
+  for (int i = 0; i < 4; ++i) dk[i] *= 0.25f;
+  float* po = dQKV + ro * 3 * D + D + h * 16 + c;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (jo + i < N) {
+      po[i * 3 * D] = dk[i];
+      po[i * 3 * D + D] = dv[i];
     }
-  }
+  float* pt = T + (int64_t)(D + h * 16 + c) * ldT + ro;
+  store_rows4(pt, dk, N - jo);
+  store_rows4(pt + (int64_t)D * ldT, dv, N - jo);
 }
 
 }  // namespace fvan

@@ -48,7 +48,6 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxVocab = 256;
-#define FVAN_INLINE __attribute__((always_inline))
 
 // KM: samples per workgroup, 32 (two 16-row MFMA tiles: every weight fragment
 // feeds both) or 16 (one tile; twice the workgroups for a batch).

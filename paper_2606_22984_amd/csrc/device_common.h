@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// on a lambda: inlined whatever its size
+#define FVAN_INLINE __attribute__((always_inline))
+
 namespace fvan {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;

@@ -243,3 +243,21 @@ def test_backward_at_the_edges_of_the_partial_sums(batch):
     torch.cuda.synchronize()
     ref = estimator.grad_surrogate(theta, cfg, spins, w.astype(np.float32).astype(np.float64))
     assert _rel(to_np(m.grads).astype(np.float64), ref) <= GRAD_TOL[FP32]
+
+
+@pytest.mark.parametrize("prec", [FP32, SPLIT])
+@pytest.mark.parametrize("n,window,prefix,batch", [(1, 1, 1, 3), (18, 3, 2, 1), (63, 70, 1, 3), (130, 16, 64, 2),
+                                                   (130, 130, 5, 3), (193, 65, 70, 1)])
+def test_backward_at_the_edges_of_attention_and_row_tiles(n, window, prefix, batch, prec):
+    """Gradient where blocks of 64 keys are all full, cut by the band, the prefix or the end, where the
+    last group of four rows is cut at a sample's end, and where a row workgroup's last waves have no rows."""
+    cfg = ModelConfig(n, 64, 2, 4).with_mask(window, prefix)
+    m, theta = make_model(cfg, batch, prec, seed=9)
+    spins = random_spins(batch, n, 10)
+    w = np.random.default_rng(2).standard_normal(batch).astype(np.float32) / batch
+    s = torch.as_tensor(spins, device="cuda")
+    ref = estimator.grad_surrogate(theta, cfg, spins, w.astype(np.float64))
+    m.grads.zero_()
+    m.log_prob_backward(s, torch.as_tensor(w, device="cuda"))
+    torch.cuda.synchronize()
+    assert _rel(to_np(m.grads).astype(np.float64), ref) <= GRAD_TOL[prec]
