@@ -22,22 +22,35 @@
 namespace fvan {
 
 // ---------------------------------------------------------------- embedding
-__global__ void embed_kernel(const float* __restrict__ theta, int64_t pos_off, int dt, int D, int N,
-                             const int8_t* __restrict__ spins, int64_t rows, float* __restrict__ X) {
-  const int64_t total = rows * D;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = i / D;
-    const int k = (int)(i % D);
-    const int t = (int)(r % N);
-    float v;
-    if (k < dt) {
-      const int tok = t == 0 ? 0 : (spins[r - 1] + 1) >> 1;
-      v = theta[tok * dt + k];
-    } else {
-      v = theta[pos_off + (int64_t)t * (D - dt) + (k - dt)];
-    }
-    X[i] = v;
+// X[r] = [token row of the row's input | position row], four features per thread and
+// one 16-byte store; the position t = r mod N is carried from row to row instead of
+// divided out (64-bit divisions per element took 4x the time of the stores).
+// token(r, t): the row's token id.
+template <typename F>
+__device__ __forceinline__ void embed_rows(const float* __restrict__ theta, int64_t pos_off, int dt, int D, int N,
+                                           int64_t rows, float* __restrict__ X, F&& token) {
+  const int D4 = D / 4, per = blockDim.x / D4;           // rows a workgroup covers at once
+  const int k = 4 * (threadIdx.x % D4), lr = threadIdx.x / D4;
+  int64_t r = blockIdx.x * (int64_t)per + lr;
+  const int64_t step = (int64_t)gridDim.x * per;
+  int t = (int)(r % N);
+  const int tstep = (int)(step % N);
+  for (; r < rows; r += step) {
+    const int tok = token(r, t);
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      v[i] = theta[k + i < dt ? (int64_t)tok * dt + k + i : pos_off + (int64_t)t * (D - dt) + (k + i - dt)];
+    *reinterpret_cast<float4*>(X + r * D + k) = make_float4(v[0], v[1], v[2], v[3]);
+    t += tstep;
+    if (t >= N) t -= N;
   }
+}
+
+__global__ __launch_bounds__(256) void embed_kernel(const float* __restrict__ theta, int64_t pos_off, int dt, int D,
+                                                    int N, const int8_t* __restrict__ spins, int64_t rows,
+                                                    float* __restrict__ X) {
+  embed_rows(theta, pos_off, dt, D, N, rows, X, [&](int64_t r, int t) { return t == 0 ? 0 : (spins[r - 1] + 1) >> 1; });
 }
 
 // ---------------------------------------------------------------- head
@@ -82,22 +95,11 @@ __global__ __launch_bounds__(256) void head_fwd_kernel(const float* __restrict__
 // Embedding of a token sequence: position t is fed tok_{t-1} (start token 0 at
 // t = 0).  A token >= vocab is clamped for the table read (its sample's ln q is
 // NaN, set by the head below), so no read leaves the token table.
-__global__ void embed_tokens_kernel(const float* __restrict__ theta, int64_t pos_off, int dt, int D, int N, int V,
-                                    const uint8_t* __restrict__ tokens, int64_t rows, float* __restrict__ X) {
-  const int64_t total = rows * D;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = i / D;
-    const int k = (int)(i % D);
-    const int t = (int)(r % N);
-    float v;
-    if (k < dt) {
-      const int tok = t == 0 ? 0 : min((int)tokens[r - 1], V - 1);
-      v = theta[tok * dt + k];
-    } else {
-      v = theta[pos_off + (int64_t)t * (D - dt) + (k - dt)];
-    }
-    X[i] = v;
-  }
+__global__ __launch_bounds__(256) void embed_tokens_kernel(const float* __restrict__ theta, int64_t pos_off, int dt,
+                                                           int D, int N, int V, const uint8_t* __restrict__ tokens,
+                                                           int64_t rows, float* __restrict__ X) {
+  embed_rows(theta, pos_off, dt, D, N, rows, X,
+             [&](int64_t r, int t) { return t == 0 ? 0 : min((int)tokens[r - 1], V - 1); });
 }
 
 // Vocab-way head: one workgroup per sample, thread v computes the logit
@@ -234,7 +236,7 @@ static hipError_t forward_chunk_t(fvan_model* m, const int8_t* spins, int nsamp,
                                   hipStream_t s) {
   const fvan_model_config& c = m->cfg;
   const int64_t rows = (int64_t)nsamp * c.n_spins;
-  const int grid = (int)std::min<int64_t>((rows * D + 255) / 256, 65536);
+  const int grid = (int)std::min<int64_t>((rows * D + 1023) / 1024, 16384);
   hipLaunchKernelGGL(embed_kernel, dim3(grid), dim3(256), 0, s, m->params, m->po.pos, c.d_token, D, c.n_spins,
                      spins, rows, m->fw.X);
   for (int l = 0; l < c.n_layers; ++l) {
@@ -253,7 +255,7 @@ template <int MODE, int D>
 static hipError_t forward_chunk_tokens_t(fvan_model* m, const uint8_t* tokens, int nsamp, float* logq, hipStream_t s) {
   const fvan_model_config& c = m->cfg;
   const int64_t rows = (int64_t)nsamp * c.n_spins;
-  const int grid = (int)std::min<int64_t>((rows * D + 255) / 256, 65536);
+  const int grid = (int)std::min<int64_t>((rows * D + 1023) / 1024, 16384);
   hipLaunchKernelGGL(embed_tokens_kernel, dim3(grid), dim3(256), 0, s, m->params, m->po.pos, c.d_token, D, c.n_spins,
                      c.vocab, tokens, rows, m->fw.X);
   for (int l = 0; l < c.n_layers; ++l) {
