@@ -153,7 +153,9 @@ __global__ void colsum_final_kernel(const float* __restrict__ part2, int width, 
 
 // Both levels for n <= 8 kColSlices: 16 columns per workgroup, thread (slice group, column).
 constexpr int kColOne = 16;
-__global__ __launch_bounds__(256) void colsum_one_kernel(const float* __restrict__ part, int n, int width,
+// CHAIN: the partials come as `rows` single waves' rows, eight of which (added in order) make one.
+template <bool CHAIN>
+__global__ __launch_bounds__(256) void colsum_one_kernel(const float* __restrict__ part, int n, int rows, int width,
                                                          float* __restrict__ out) {
   __shared__ float red[kColSlices][kColOne + 1];
   const int c = threadIdx.x & (kColOne - 1), grp = threadIdx.x / kColOne;   // 16 groups of 4 slices
@@ -162,11 +164,22 @@ __global__ __launch_bounds__(256) void colsum_one_kernel(const float* __restrict
   const int per = (n + kColSlices - 1) / kColSlices;
   float v[4][8];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int u = 0; u < 8; ++u)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int q = 0; q < 4; ++q) {
       const int i = (4 * grp + q) * per + u;
-      v[q][u] = u < per && i < n ? p[(size_t)i * width] : 0.f;
+      if constexpr (CHAIN) {
+        float t[8], sum = 0.f;
+        v[q][u] = 0.f;
+        if (u >= per) continue;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) t[w] = p[(size_t)min(8 * i + w, rows - 1) * width];
+#pragma unroll
+        for (int w = 0; w < 8; ++w) sum += 8 * i + w < rows ? t[w] : 0.f;
+        v[q][u] = i < n ? sum : 0.f;
+      } else {
+        v[q][u] = u < per && i < n ? p[(size_t)i * width] : 0.f;
+      }
     }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -187,11 +200,24 @@ __global__ __launch_bounds__(256) void colsum_one_kernel(const float* __restrict
 
 static void colsum_add(const float* part, int n, int width, float* part2, float* out, hipStream_t s) {
   if (n <= 8 * kColSlices) {
-    hipLaunchKernelGGL(colsum_one_kernel, dim3((width + kColOne - 1) / kColOne), dim3(256), 0, s, part, n, width, out);
+    hipLaunchKernelGGL(colsum_one_kernel<false>, dim3((width + kColOne - 1) / kColOne), dim3(256), 0, s, part, n, n, width,
+                       out);
     return;
   }
   hipLaunchKernelGGL(colsum_slices_kernel, dim3((width + 63) / 64, kColSlices), dim3(256), 0, s, part, n, width, part2);
   hipLaunchKernelGGL(colsum_final_kernel, dim3((width + 63) / 64), dim3(64), 0, s, (const float*)part2, width, out);
+}
+
+// The LayerNorm gain and shift partials of a row kernel over `rows` rows: one per 128 rows,
+// or (few) one per 16.
+static void ln_colsum_add(const float* part, int64_t rows, bool few, int width, float* part2, float* out,
+                          hipStream_t s) {
+  const int n = (int)((rows + 127) / 128);
+  if (few)   // at most 1024 workgroups of 64 rows: n <= 8 kColSlices
+    hipLaunchKernelGGL(colsum_one_kernel<true>, dim3((width + kColOne - 1) / kColOne), dim3(256), 0, s, part, n,
+                       (int)((rows + 63) / 64) * 4, width, out);
+  else
+    colsum_add(part, n, width, part2, out, s);
 }
 
 // ---------------------------------------------------------------- transpose + cast
@@ -856,6 +882,7 @@ static hipError_t backward_chunk_t(fvan_model* m, const void* seq, int nsamp, co
   // joined the side stream back before returning), so the fork and join also
   // hold under stream capture.
   hipStream_t ss = f.side;
+  const bool few = few_rows(rows, device_cus(m->device));
   hipEvent_t ffn_ready = f.ev[0], ffn_read = f.ev[1], qkv_ready = f.ev[2], qkv_read = f.ev[3];
   for (int l = L - 1; l >= 0; --l) {
     const float* lp = m->params + m->po.layer0 + (int64_t)l * m->po.layer_stride;
@@ -869,11 +896,17 @@ static hipError_t backward_chunk_t(fvan_model* m, const void* seq, int nsamp, co
     // differentiates through W2, GELU' and W1 and the LayerNorm, and leaves the
     // feature-major operands of the two weight gradients
     if (l < L - 1 && (err = hipStreamWaitEvent(s, ffn_read, 0))) return err;   // recorded by layer l + 1
-    hipLaunchKernelGGL((ffn_bwd_fused_kernel<MODE, D>), dim3((int)((rows + kFfnBwdRows - 1) / kFfnBwdRows)),
-                       dim3(512), 0, s, XM, (const float*)f.dX, lp + m->po.ln2_g, lp + m->po.ln2_b, rows,
-                       reinterpret_cast<const uint4*>(wl + m->pk.ffn1), reinterpret_cast<const uint4*>(wl + m->pk.ffn2T),
-                       reinterpret_cast<const uint4*>(wl + m->pk.ffn1T), lp + m->po.ffn1_b, (AT*)f.T_b, (AT*)f.T_a,
-                       (AT*)f.T_c, (AT*)f.T_d, f.ldT, f.dXM, f.colpart);
+    auto ffn_bwd = [&](auto waves) {
+      constexpr int NW = decltype(waves)::value, R = 16 * NW;
+      hipLaunchKernelGGL((ffn_bwd_fused_kernel<MODE, D, NW>), dim3((int)((rows + R - 1) / R)), dim3(64 * NW), 0, s, XM,
+                         (const float*)f.dX, lp + m->po.ln2_g, lp + m->po.ln2_b, rows,
+                         reinterpret_cast<const uint4*>(wl + m->pk.ffn1),
+                         reinterpret_cast<const uint4*>(wl + m->pk.ffn2T),
+                         reinterpret_cast<const uint4*>(wl + m->pk.ffn1T), lp + m->po.ffn1_b, (AT*)f.T_b, (AT*)f.T_a,
+                         (AT*)f.T_c, (AT*)f.T_d, f.ldT, f.dXM, f.colpart);
+    };
+    if (few) ffn_bwd(std::integral_constant<int, 4>());
+    else ffn_bwd(std::integral_constant<int, 8>());
     if ((err = hipEventRecord(ffn_ready, s))) return err;
     if ((err = hipStreamWaitEvent(ss, ffn_ready, 0))) return err;
     if ((err = wgrad<MODE, D, 4 * D>(m, f.T_d, f.T_b, rows, gl + m->po.ffn2_w, gl + m->po.ffn2_b, ss, D, f.part2)))
@@ -882,7 +915,7 @@ static hipError_t backward_chunk_t(fvan_model* m, const void* seq, int nsamp, co
                                      f.part2)))
       return err;
     if ((err = hipEventRecord(ffn_read, ss))) return err;
-    colsum_add(f.colpart, (int)((rows + kFfnBwdRows - 1) / kFfnBwdRows), 2 * D, f.colpart2, gl + m->po.ln2_g, s);
+    ln_colsum_add(f.colpart, rows, few, 2 * D, f.colpart2, gl + m->po.ln2_g, s);
     // ---- attention backward (dO = dXM: the heads' output is added to the residual directly);
     // probabilities are recomputed from Q, K and the saved log-sum-exp
     if (l < L - 1 && (err = hipStreamWaitEvent(s, qkv_read, 0))) return err;   // recorded by layer l + 1
@@ -912,15 +945,21 @@ static hipError_t backward_chunk_t(fvan_model* m, const void* seq, int nsamp, co
     }
     // ---- QKV backward: dA1 = dQKV W_qkv and the LN1 backward in one kernel, which
     // also leaves LN1(x) feature-major for the W_qkv gradient
-    hipLaunchKernelGGL((gemm_ln_bwd_kernel<MODE, D, 3 * D>), dim3((int)((rows + kGlbRows - 1) / kGlbRows)), dim3(512),
-                       0, s, (const float*)f.dQKV, rows, reinterpret_cast<const uint4*>(wl + m->pk.qkvT), X,
-                       lp + m->po.ln1_g, lp + m->po.ln1_b, (const float*)f.dXM, f.dX, (float*)f.T_f, f.ldT, f.colpart);
+    auto qkv_bwd = [&](auto waves) {
+      constexpr int NW = decltype(waves)::value, R = 16 * NW;
+      hipLaunchKernelGGL((gemm_ln_bwd_kernel<MODE, D, 3 * D, NW>), dim3((int)((rows + R - 1) / R)), dim3(64 * NW), 0, s,
+                         (const float*)f.dQKV, rows, reinterpret_cast<const uint4*>(wl + m->pk.qkvT), X,
+                         lp + m->po.ln1_g, lp + m->po.ln1_b, (const float*)f.dXM, f.dX, (float*)f.T_f, f.ldT,
+                         f.colpart);
+    };
+    if (few) qkv_bwd(std::integral_constant<int, 4>());
+    else qkv_bwd(std::integral_constant<int, 8>());
     if ((err = hipEventRecord(qkv_ready, s))) return err;
     if ((err = hipStreamWaitEvent(ss, qkv_ready, 0))) return err;
     if ((err = wgrad<MODE, 3 * D, D>(m, f.T_e, f.T_f, rows, gl + m->po.qkv_w, gl + m->po.qkv_b, ss, 3 * D, f.part2)))
       return err;
     if ((err = hipEventRecord(qkv_read, ss))) return err;
-    colsum_add(f.colpart, (int)((rows + kGlbRows - 1) / kGlbRows), 2 * D, f.colpart2, gl + m->po.ln1_g, s);
+    ln_colsum_add(f.colpart, rows, few, 2 * D, f.colpart2, gl + m->po.ln1_g, s);
   }
   // join: every side-stream kernel precedes what follows on the caller's stream
   if ((err = hipStreamWaitEvent(s, qkv_read, 0))) return err;

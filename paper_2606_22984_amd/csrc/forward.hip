@@ -204,7 +204,8 @@ hipError_t forward_layer(fvan_model* m, int l, int64_t rows, int nsamp, hipStrea
   e.ln_x = X;
   e.ln_g = lp + m->po.ln1_g;
   e.ln_b = lp + m->po.ln1_b;
-  hipError_t err = gemm_rows<MODE, D, 3 * D, EPI_STORE_KV>(nullptr, rows, wl + m->pk.qkv, e, s);
+  const bool few = few_rows(rows, device_cus(m->device));
+  hipError_t err = gemm_rows<MODE, D, 3 * D, EPI_STORE_KV>(nullptr, rows, wl + m->pk.qkv, e, s, few);
   if (err != hipSuccess) return err;
   const int H = c.n_heads, dh = D / H;
   const int ggrid = (c.n_spins + kGenRows - 1) / kGenRows * H * nsamp;
@@ -224,10 +225,16 @@ hipError_t forward_layer(fvan_model* m, int l, int64_t rows, int nsamp, hipStrea
       hipLaunchKernelGGL((attn_fwd_gen<KT, 64>), dim3(ggrid), dim3(kGenThreads), 0, s, (const KT*)QKV, X, XM, LSE,
                          c.n_spins, D, H, c.window, m->kg.P);
   }
-  hipLaunchKernelGGL((ffn_fused_kernel<MODE, D>), dim3((int)((rows + kFfnRows - 1) / kFfnRows)), dim3(512), 0, s,
-                     (const float*)XM, lp + m->po.ln2_g, lp + m->po.ln2_b, rows,
-                     reinterpret_cast<const uint4*>(wl + m->pk.ffn1), reinterpret_cast<const uint4*>(wl + m->pk.ffn2),
-                     lp + m->po.ffn1_b, lp + m->po.ffn2_b, (const float*)XM, Xn);
+  auto ffn = [&](auto waves) {
+    constexpr int NW = decltype(waves)::value, R = 16 * NW;
+    hipLaunchKernelGGL((ffn_fused_kernel<MODE, D, NW>), dim3((int)((rows + R - 1) / R)), dim3(64 * NW), 0, s,
+                       (const float*)XM, lp + m->po.ln2_g, lp + m->po.ln2_b, rows,
+                       reinterpret_cast<const uint4*>(wl + m->pk.ffn1),
+                       reinterpret_cast<const uint4*>(wl + m->pk.ffn2), lp + m->po.ffn1_b, lp + m->po.ffn2_b,
+                       (const float*)XM, Xn);
+  };
+  if (few) ffn(std::integral_constant<int, 4>());
+  else ffn(std::integral_constant<int, 8>());
   return hipGetLastError();
 }
 

@@ -50,6 +50,9 @@ static int allocate_fwd(fvan_model* m, hipStream_t s) {
   const size_t kt = kv_elem_bytes(c.precision);
   f.part_floats = (size_t)512 * 4 * D * (D + 16);
   f.colpart_floats = std::max<size_t>((size_t)f.chunk * (2 * D + 2), ((R + 63) / 64) * 2 * D);
+  // few rows (at most 64 per CU): a row of partials per 16 rows
+  f.colpart_floats = std::max<size_t>(f.colpart_floats,
+                                      std::min<size_t>((R + 63) / 64, device_cus(m->device)) * 4 * 2 * D);
   struct A { void** p; size_t bytes; const char* what; } allocs[] = {
       {(void**)&f.X, (size_t)(L + 1) * R * D * 4, "X"},   {(void**)&f.XM, (size_t)L * R * D * 4, "XM"},
       {(void**)&f.LSE, (size_t)L * R * H * 4, "LSE"},

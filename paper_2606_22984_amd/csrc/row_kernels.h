@@ -12,6 +12,8 @@
 
 namespace fvan {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // ---------------------------------------------------------------- LayerNorm
 // 64 rows per workgroup, 16 lanes per row.  Optional outputs: row-major `out`
 // [rows x D] and feature-major `outT` [D x ldT] (element (r, k) at k*ldT + r).
@@ -207,7 +209,15 @@ __device__ __forceinline__ void store4(T* p, float a, float b, float c, float d)
 // GELU / GELU' epilogues, where the larger tile halves the occupancy.
 template <int EPI> struct StagedRowTiles { static constexpr int value = EPI == EPI_STORE_KV ? 2 : 1; };
 
-template <int MODE, int K, int NOUT, int EPI>
+// Few rows: workgroups of 64 rows (four 16-row tiles) instead of 128 in the row kernels,
+// as long as these find a CU each: below one workgroup per CU, 128 rows only leave CUs
+// idle while two waves share a SIMD's matrix core.  Gradient of two layers with 128 and
+// with 64 rows: 371 -> 316 us at 4096 rows, 445 -> 388 at 16384 (d = 64, FP32), 1148 -> 872
+// (d = 128, FP32), 605 -> 589 (d = 128, split); past one workgroup per CU, at 17600 rows,
+// 626 -> 720 (d = 128, split) and 459 -> 463 (d = 64, FP32).
+inline bool few_rows(int64_t rows, int cus) { return (rows + 63) / 64 <= std::min(cus, 1024); }
+
+template <int MODE, int K, int NOUT, int EPI, int RT>
 __global__ __launch_bounds__(256) void gemm_rows_staged_kernel(const typename Mode<MODE>::ActT* __restrict__ A,
                                                                int64_t rows, const uint4* __restrict__ pack,
                                                                EpiArgs e) {
@@ -220,8 +230,7 @@ __global__ __launch_bounds__(256) void gemm_rows_staged_kernel(const typename Mo
   constexpr int LK = KC / 4;
   constexpr int NC = K / KC;
   constexpr int NG = NOUT / 64;
-  constexpr int RT = StagedRowTiles<EPI>::value; // 16-row tiles per wave
-  constexpr int R = 64 * RT;                     // rows per workgroup
+  constexpr int R = 64 * RT;                     // rows per workgroup: RT 16-row tiles per wave
   constexpr size_t LO = (size_t)NOUT * K / 8;
   __shared__ __align__(16) float Ev[R][68];                               // out / outT values
   __shared__ __align__(16) float Eh[EPI == EPI_STORE_KV ? 1 : R][68];     // GELU: hpre_out; GELU': hpre_in
@@ -248,7 +257,7 @@ __global__ __launch_bounds__(256) void gemm_rows_staged_kernel(const typename Mo
   const bool full = r0 + R <= rows;
   OT* out = reinterpret_cast<OT*>(e.out);
   AT* outT = reinterpret_cast<AT*>(e.outT);
-  for (int ng = 0; ng < NG; ++ng) {
+  for (int ng = blockIdx.y; ng < NG; ng += gridDim.y) {
     if constexpr (EPI == EPI_DGELU) {
       // stage the pre-activation tile (256-byte row segments)
 #pragma unroll
@@ -328,7 +337,7 @@ __global__ __launch_bounds__(256) void gemm_rows_staged_kernel(const typename Mo
 // Fused feed-forward block of the teacher-forced forward pass:
 //   out[r] = resid[r] + W2 GELU(W1 a[r] + b1) + b2,   W1 [4D x D], W2 [D x 4D],
 // a[r] = LayerNorm(X rows; ln_g, ln_b) computed in the kernel.
-// 128 rows per workgroup, one 16-row MFMA tile per wave (8 waves).  The hidden
+// 128 rows per workgroup (few rows: 64), one 16-row MFMA tile per wave (NW waves).  The hidden
 // layer is walked 32 units at a time: the chunk's fragments of W1 (its rows)
 // and W2 (its columns) are staged in LDS once for all eight waves, the next
 // chunk's fetched into registers meanwhile, and each wave's hidden activations
@@ -342,16 +351,13 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-constexpr int kFfnRows = 128;                // rows per fused-FFN workgroup
-
-template <int MODE, int D>
-__global__ __launch_bounds__(512, 4) void ffn_fused_kernel(const float* __restrict__ X, const float* __restrict__ ln_g,
+template <int MODE, int D, int NW = 8>
+__global__ __launch_bounds__(64 * NW, NW / 2) void ffn_fused_kernel(const float* __restrict__ X, const float* __restrict__ ln_g,
                                                         const float* __restrict__ ln_b, int64_t rows,
                                                         const uint4* __restrict__ p1, const uint4* __restrict__ p2,
                                                         const float* __restrict__ b1, const float* __restrict__ b2,
                                                         const float* __restrict__ resid, float* __restrict__ out) {
   typedef typename Mode<MODE>::ActT AT;
-  constexpr int NW = 8;                      // waves
   constexpr int KC = Mode<MODE>::KC;
   constexpr int LK = KC / 4;
   constexpr int NPL = Mode<MODE>::SPLIT ? 2 : 1;   // weight planes (hi, lo)
@@ -366,15 +372,14 @@ __global__ __launch_bounds__(512, 4) void ffn_fused_kernel(const float* __restri
   constexpr int S1 = NT1 * NC1 * 64;         // fragments of a W1 chunk, per plane
   constexpr int S2 = NT2 * NC2H * 64;        // fragments of a W2 chunk, per plane
   constexpr int SW = S1 + S2;
-  constexpr int NPRE = (NPL * SW + 64 * NW - 1) / (64 * NW);
-  static_assert(NPRE <= 4, "at most four staged fragments per thread");
-  static_assert(64 * NW == 512, "staging strides assume 512 threads");
+  constexpr int NTH = 64 * NW;
+  constexpr int NPRE = (NPL * SW + NTH - 1) / NTH;
   constexpr int LDH = HC + 4;
   __shared__ __align__(16) uint4 Ws[NPL][SW];      // [W1 chunk | W2 chunk]
   __shared__ __align__(16) AT Hs[NW][16][LDH];
   __shared__ float Bh[4 * D];                // b1
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, c = lane & 15;
-  const int64_t rbase = (int64_t)blockIdx.x * kFfnRows + wave * 16;
+  const int64_t rbase = ((int64_t)blockIdx.x * NW + wave) * 16;
   auto src = [&](int hc, int idx) -> const uint4* {
     const int pl = idx / SW, j = idx % SW;
     const size_t lo = pl ? LO : 0;
@@ -382,32 +387,29 @@ __global__ __launch_bounds__(512, 4) void ffn_fused_kernel(const float* __restri
     const int k = j - S1, t2 = k / (NC2H * 64), rest = k % (NC2H * 64);
     return p2 + ((size_t)t2 * NC2 + (size_t)hc * NC2H) * 64 + rest + lo;
   };
-  uint4 q0{}, q1{}, q2{}, q3{};
-#define FVAN_FF_FETCH(hc)                                                            \
-  do {                                                                               \
-    if (NPRE > 0 && tid < NPL * SW) q0 = *src(hc, tid);                              \
-    if (NPRE > 1 && tid + 512 < NPL * SW) q1 = *src(hc, tid + 512);                  \
-    if (NPRE > 2 && tid + 1024 < NPL * SW) q2 = *src(hc, tid + 1024);                \
-    if (NPRE > 3 && tid + 1536 < NPL * SW) q3 = *src(hc, tid + 1536);                \
-  } while (0)
-#define FVAN_FF_COMMIT()                                                             \
-  do {                                                                               \
-    uint4* w = &Ws[0][0];                                                            \
-    if (NPRE > 0 && tid < NPL * SW) w[tid] = q0;                                     \
-    if (NPRE > 1 && tid + 512 < NPL * SW) w[tid + 512] = q1;                         \
-    if (NPRE > 2 && tid + 1024 < NPL * SW) w[tid + 1024] = q2;                       \
-    if (NPRE > 3 && tid + 1536 < NPL * SW) w[tid + 1536] = q3;                       \
-  } while (0)
+  u32x4 pre[NPRE];
+  auto fetch = [&](int hc) FVAN_INLINE {
+#pragma unroll
+    for (int u = 0; u < NPRE; ++u)
+      pre[u] = *reinterpret_cast<const u32x4*>(src(hc, NTH * (u + 1) <= NPL * SW ? tid + NTH * u : std::min(tid + NTH * u, NPL * SW - 1)));
+    __builtin_amdgcn_sched_barrier(0);   // issued here, not where the registers are wanted
+  };
+  auto commit = [&]() FVAN_INLINE {
+    u32x4* w = reinterpret_cast<u32x4*>(&Ws[0][0]);
+#pragma unroll
+    for (int u = 0; u < NPRE; ++u)
+      if (NTH * (u + 1) <= NPL * SW || tid + NTH * u < NPL * SW) w[tid + NTH * u] = pre[u];
+  };
   for (int k = tid; k < 4 * D; k += 64 * NW) Bh[k] = b1[k];
-  FVAN_FF_FETCH(0);
+  fetch(0);
   FragA<MODE> fa[NC1];                       // the wave's A fragments, converted once (rows clamped)
   load_ln_frags<MODE, D>(X, std::min<int64_t>(rbase + c, rows - 1), ln_g, ln_b, g, fa);
   floatx4 acc2[NT2];
 #pragma unroll
   for (int t = 0; t < NT2; ++t) acc2[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  FVAN_FF_COMMIT();
+  commit();
   __syncthreads();
-  if (NH > 1) FVAN_FF_FETCH(1);
+  if (NH > 1) fetch(1);
   AT (*H)[LDH] = Hs[wave];
   const uint4* W1s = &Ws[0][0];
   const uint4* W2s = &Ws[0][S1];
@@ -438,13 +440,11 @@ __global__ __launch_bounds__(512, 4) void ffn_fused_kernel(const float* __restri
     }
     __syncthreads();                         // every wave is done with this chunk's weights and tiles
     if (hc + 1 < NH) {
-      FVAN_FF_COMMIT();
+      commit();
       __syncthreads();
-      if (hc + 2 < NH) FVAN_FF_FETCH(hc + 2);
+      if (hc + 2 < NH) fetch(hc + 2);
     }
   }
-#undef FVAN_FF_FETCH
-#undef FVAN_FF_COMMIT
 #pragma unroll
   for (int t = 0; t < NT2; ++t) {
     const int n = t * 16 + c;
@@ -567,6 +567,25 @@ __device__ __forceinline__ void ln_bwd_rows(floatx4 (&acc)[D / 16], LnRows<D>& i
   }
 }
 
+// The column sums of a workgroup's waves (red) into part: with eight waves their sum, one
+// row of partials per 128 rows of the pass; with four (few rows) each wave's own row, which
+// the reduction adds eight at a time in the same order.
+template <int D, int NW>
+__device__ __forceinline__ void store_col_part(const float (*red)[2 * D], float* __restrict__ part) {
+  static_assert(NW == 8 || NW == 4, "one or half a group of eight waves");
+  __syncthreads();
+  if constexpr (NW == 8) {
+    for (int k = threadIdx.x; k < 2 * D; k += 64 * NW) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) sum += red[w][k];
+      part[(size_t)blockIdx.x * 2 * D + k] = sum;
+    }
+  } else {
+    for (int i = threadIdx.x; i < NW * 2 * D; i += 64 * NW) part[(size_t)blockIdx.x * NW * 2 * D + i] = red[0][i];
+  }
+}
+
 // Fused feed-forward backward of one layer, with the block's forward recomputed
 // in place (x = the post-attention residual XM, dY = the gradient arriving at
 // the block's output):
@@ -576,7 +595,7 @@ __device__ __forceinline__ void ln_bwd_rows(floatx4 (&acc)[D / 16], LnRows<D>& i
 // plus the feature-major operands of the weight gradients, Gt = g^T and
 // dHt = dH^T [4D x ldT], At = a^T and dYt = dY^T [D x ldT], and per-workgroup
 // partial sums of the LN2 gain and shift gradients (part[block][2D]).
-// 128 rows per workgroup, one 16-row MFMA tile per wave (8 waves).  The hidden
+// 128 rows per workgroup (few rows: 64), one 16-row MFMA tile per wave (NW waves).  The hidden
 // layer is walked 32 units at a time: the chunk's weight fragments (rows of W1
 // and W2^T, columns of W1^T) are staged in LDS once for all eight waves, in two
 // alternating buffers so that the next chunk is committed while the current one
@@ -594,10 +613,8 @@ __device__ __forceinline__ void ln_bwd_rows(floatx4 (&acc)[D / 16], LnRows<D>& i
 // backward are loaded during the last chunk.  1M rows, d = 128, split: 2.30 -> 2.10 ms
 // (4.9 GB written and 2.1 GB read: 1.4 ms at the rate of a copy).
 // p1: W1 [4D x D] pack; p2t: W2^T [4D x D] pack; p1t: W1^T [D x 4D] pack.
-constexpr int kFfnBwdRows = 128;
-
-template <int MODE, int D>
-__global__ __launch_bounds__(512) void ffn_bwd_fused_kernel(
+template <int MODE, int D, int NW = 8>
+__global__ __launch_bounds__(64 * NW) void ffn_bwd_fused_kernel(
     const float* __restrict__ X, const float* __restrict__ dY, const float* __restrict__ ln_g,
     const float* __restrict__ ln_b, int64_t rows, const uint4* __restrict__ p1, const uint4* __restrict__ p2t,
     const uint4* __restrict__ p1t, const float* __restrict__ b1, typename Mode<MODE>::ActT* __restrict__ Gt,
@@ -605,7 +622,6 @@ __global__ __launch_bounds__(512) void ffn_bwd_fused_kernel(
     typename Mode<MODE>::ActT* __restrict__ dYt, int64_t ldT, float* __restrict__ out, float* __restrict__ part) {
   typedef typename Mode<MODE>::ActT AT;
   static_assert(sizeof(AT) == 4, "FP32 activations");
-  constexpr int NW = 8;                      // waves
   constexpr int KC = Mode<MODE>::KC;
   constexpr int LK = KC / 4;
   constexpr int NPL = Mode<MODE>::SPLIT ? 2 : 1;   // weight planes (hi, lo)
@@ -620,14 +636,15 @@ __global__ __launch_bounds__(512) void ffn_bwd_fused_kernel(
   constexpr int S1 = NT1 * NC1 * 64;         // fragments of a W1 (or W2^T) chunk, per plane
   constexpr int S3 = NT2 * NC2H * 64;        // fragments of a W1^T chunk, per plane
   constexpr int SW = 2 * S1 + S3;
-  constexpr int NPRE = (NPL * SW + 64 * NW - 1) / (64 * NW);   // staged fragments per thread
+  constexpr int NTH = 64 * NW;
+  constexpr int NPRE = (NPL * SW + NTH - 1) / NTH;   // staged fragments per thread
   constexpr int LDH = HC + 4;
   __shared__ __align__(16) uint4 Ws[2][NPL][SW];   // two stages of [W1 chunk | W2^T chunk | W1^T chunk]
   __shared__ __align__(16) float Hd[NW][16][LDH];
   __shared__ float red[NW][2 * D];
   __shared__ float Bh[4 * D];                // b1
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, c = lane & 15;
-  const int64_t rbase = (int64_t)blockIdx.x * kFfnBwdRows + wave * 16;
+  const int64_t rbase = ((int64_t)blockIdx.x * NW + wave) * 16;
   // the 16 rows whose hidden activations the wave computes and stores: a wave past the
   // end repeats the last group's, so that the loop below has no branch around a store
   const int64_t rb = std::min<int64_t>(rbase, (rows - 1) & ~(int64_t)15);
@@ -640,32 +657,22 @@ __global__ __launch_bounds__(512) void ffn_bwd_fused_kernel(
     const int k = j - 2 * S1, t2 = k / (NC2H * 64), rest = k % (NC2H * 64);
     return p1t + ((size_t)t2 * NC2 + (size_t)hc * NC2H) * 64 + rest + lo;
   };
-  // the next chunk's fragments, held in registers (p0..p5) between the fetch and the commit
-  static_assert(NPRE <= 6, "at most six staged fragments per thread");
-  uint4 p0{}, p1r{}, p2r{}, p3{}, p4{}, p5{};
-#define FVAN_FB_FETCH(hc)                                                            \
-  do {                                                                               \
-    const int i0 = tid;                                                              \
-    if (NPRE > 0 && i0 < NPL * SW) p0 = *src(hc, i0);                                \
-    if (NPRE > 1 && i0 + 512 < NPL * SW) p1r = *src(hc, i0 + 512);                   \
-    if (NPRE > 2 && i0 + 1024 < NPL * SW) p2r = *src(hc, i0 + 1024);                 \
-    if (NPRE > 3 && i0 + 1536 < NPL * SW) p3 = *src(hc, i0 + 1536);                  \
-    if (NPRE > 4 && i0 + 2048 < NPL * SW) p4 = *src(hc, i0 + 2048);                  \
-    if (NPRE > 5 && i0 + 2560 < NPL * SW) p5 = *src(hc, i0 + 2560);                  \
-  } while (0)
-#define FVAN_FB_COMMIT(buf)                                                          \
-  do {                                                                               \
-    uint4* w = &Ws[buf][0][0];                                                       \
-    if (NPRE > 0 && tid < NPL * SW) w[tid] = p0;                                     \
-    if (NPRE > 1 && tid + 512 < NPL * SW) w[tid + 512] = p1r;                        \
-    if (NPRE > 2 && tid + 1024 < NPL * SW) w[tid + 1024] = p2r;                      \
-    if (NPRE > 3 && tid + 1536 < NPL * SW) w[tid + 1536] = p3;                       \
-    if (NPRE > 4 && tid + 2048 < NPL * SW) w[tid + 2048] = p4;                       \
-    if (NPRE > 5 && tid + 2560 < NPL * SW) w[tid + 2560] = p5;                       \
-  } while (0)
-  static_assert(64 * NW == 512, "staging strides assume 512 threads");
+  // the next chunk's fragments, held in registers between the fetch and the commit
+  u32x4 pre[NPRE];
+  auto fetch = [&](int hc) FVAN_INLINE {
+#pragma unroll
+    for (int u = 0; u < NPRE; ++u)
+      pre[u] = *reinterpret_cast<const u32x4*>(src(hc, NTH * (u + 1) <= NPL * SW ? tid + NTH * u : std::min(tid + NTH * u, NPL * SW - 1)));
+    __builtin_amdgcn_sched_barrier(0);   // issued here, not where the registers are wanted
+  };
+  auto commit = [&](int buf) FVAN_INLINE {
+    u32x4* w = reinterpret_cast<u32x4*>(&Ws[buf][0][0]);
+#pragma unroll
+    for (int u = 0; u < NPRE; ++u)
+      if (NTH * (u + 1) <= NPL * SW || tid + NTH * u < NPL * SW) w[tid + NTH * u] = pre[u];
+  };
   for (int k = tid; k < 4 * D; k += 64 * NW) Bh[k] = b1[k];
-  FVAN_FB_FETCH(0);
+  fetch(0);
   // A fragments of the wave's rows (clamped; every output below is guarded)
   const int64_t ra = std::min<int64_t>(rb + c, rows - 1);
   FragA<MODE> fa[NC1], fy[NC1];
@@ -678,9 +685,9 @@ __global__ __launch_bounds__(512) void ffn_bwd_fused_kernel(
       *reinterpret_cast<float4*>(&af[i]) = load_nt4(dY + ra * D + cc * KC + g * LK + i);
     fy[cc].load(af);
   }
-  FVAN_FB_COMMIT(0);
+  commit(0);
   __syncthreads();
-  if (NH > 1) FVAN_FB_FETCH(1);
+  if (NH > 1) fetch(1);
   floatx4 acc[NT2];
 #pragma unroll
   for (int t = 0; t < NT2; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -730,22 +737,14 @@ __global__ __launch_bounds__(512) void ffn_bwd_fused_kernel(
     }
     // the other stage was last read in chunk hc - 1, which every wave finished
     // before the barrier that ended it
-    if (hc + 1 < NH) FVAN_FB_COMMIT((hc + 1) & 1);
+    if (hc + 1 < NH) commit((hc + 1) & 1);
     __syncthreads();                         // chunk hc + 1 is staged; stage hc & 1 is free
     // issued after the barrier, whose fence would otherwise wait for these loads
-    if (hc + 2 < NH) FVAN_FB_FETCH(hc + 2);
+    if (hc + 2 < NH) fetch(hc + 2);
   }
   // LN2 backward on the wave's rows (the workgroup's partial sums below)
   ln_bwd_rows<D>(acc, lr, ln_g, ln_b, rbase, rows, g, c, out, At, dYt, ldT, red[wave]);
-  __syncthreads();
-  for (int k = tid; k < 2 * D; k += 64 * NW) {
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) sum += red[w][k];
-    part[(size_t)blockIdx.x * 2 * D + k] = sum;
-  }
-#undef FVAN_FB_FETCH
-#undef FVAN_FB_COMMIT
+  store_col_part<D, NW>(red, part);
 }
 
 // Input gradient of the LayerNorm-fed QKV projection, in one kernel:
@@ -758,10 +757,8 @@ __global__ __launch_bounds__(512) void ffn_bwd_fused_kernel(
 // group), the group after next fetched into registers meanwhile.  Bound by HBM: each
 // wave reads its own rows of dQKV, loaded one group ahead, and x and resid, loaded
 // during the last group (1M rows, d = 128, split: 0.86 -> 0.76 ms, 3.7 GB, 4.8 TB/s).
-constexpr int kGlbRows = 128;
-
-template <int MODE, int D, int K>
-__global__ __launch_bounds__(512) void gemm_ln_bwd_kernel(const float* __restrict__ A, int64_t rows,
+template <int MODE, int D, int K, int NW = 8>
+__global__ __launch_bounds__(64 * NW) void gemm_ln_bwd_kernel(const float* __restrict__ A, int64_t rows,
                                                           const uint4* __restrict__ pack, const float* __restrict__ X,
                                                           const float* __restrict__ ln_g,
                                                           const float* __restrict__ ln_b,
@@ -770,7 +767,6 @@ __global__ __launch_bounds__(512) void gemm_ln_bwd_kernel(const float* __restric
                                                           float* __restrict__ part) {
   typedef typename Mode<MODE>::ActT AT;
   static_assert(sizeof(AT) == 4, "FP32 activations");
-  constexpr int NW = 8;
   constexpr int KC = Mode<MODE>::KC;
   constexpr int LK = KC / 4;
   constexpr int NPL = Mode<MODE>::SPLIT ? 2 : 1;
@@ -781,39 +777,31 @@ __global__ __launch_bounds__(512) void gemm_ln_bwd_kernel(const float* __restric
   constexpr int NG = NC / CG;
   constexpr size_t LO = (size_t)D * K / 8;
   constexpr int SW = NT * CG * 64;           // fragments per plane and stage
-  constexpr int NPRE = (NPL * SW + 64 * NW - 1) / (64 * NW);
-  static_assert(NPRE <= 6, "at most six staged fragments per thread");
+  constexpr int NTH = 64 * NW;
+  constexpr int NPRE = (NPL * SW + NTH - 1) / NTH;
   __shared__ __align__(16) uint4 Ws[2][NPL][SW];
   __shared__ float red[NW][2 * D];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, c = lane & 15;
-  const int64_t rbase = (int64_t)blockIdx.x * kGlbRows + wave * 16;
+  const int64_t rbase = ((int64_t)blockIdx.x * NW + wave) * 16;
   const int64_t ra = std::min<int64_t>(rbase + c, rows - 1);
   // staged fragment idx (plane, tile t, chunk cc of the group, lane) -> its place in the pack
   auto src = [&](int grp, int idx) -> const uint4* {
     const int pl = idx / SW, rem = idx % SW, t = rem / (CG * 64), r2 = rem % (CG * 64);
     return pack + ((size_t)t * NC + (size_t)grp * CG) * 64 + r2 + (pl ? LO : 0);
   };
-  uint4 q0{}, q1{}, q2{}, q3{}, q4{}, q5{};
-#define FVAN_GL_FETCH(grp)                                                           \
-  do {                                                                               \
-    if (NPRE > 0 && tid < NPL * SW) q0 = *src(grp, tid);                             \
-    if (NPRE > 1 && tid + 512 < NPL * SW) q1 = *src(grp, tid + 512);                 \
-    if (NPRE > 2 && tid + 1024 < NPL * SW) q2 = *src(grp, tid + 1024);               \
-    if (NPRE > 3 && tid + 1536 < NPL * SW) q3 = *src(grp, tid + 1536);               \
-    if (NPRE > 4 && tid + 2048 < NPL * SW) q4 = *src(grp, tid + 2048);               \
-    if (NPRE > 5 && tid + 2560 < NPL * SW) q5 = *src(grp, tid + 2560);               \
-  } while (0)
-#define FVAN_GL_COMMIT(buf)                                                          \
-  do {                                                                               \
-    uint4* w = &Ws[buf][0][0];                                                       \
-    if (NPRE > 0 && tid < NPL * SW) w[tid] = q0;                                     \
-    if (NPRE > 1 && tid + 512 < NPL * SW) w[tid + 512] = q1;                         \
-    if (NPRE > 2 && tid + 1024 < NPL * SW) w[tid + 1024] = q2;                       \
-    if (NPRE > 3 && tid + 1536 < NPL * SW) w[tid + 1536] = q3;                       \
-    if (NPRE > 4 && tid + 2048 < NPL * SW) w[tid + 2048] = q4;                       \
-    if (NPRE > 5 && tid + 2560 < NPL * SW) w[tid + 2560] = q5;                       \
-  } while (0)
-  static_assert(64 * NW == 512, "staging strides assume 512 threads");
+  u32x4 pre[NPRE];
+  auto fetch = [&](int grp) FVAN_INLINE {
+#pragma unroll
+    for (int u = 0; u < NPRE; ++u)
+      pre[u] = *reinterpret_cast<const u32x4*>(src(grp, NTH * (u + 1) <= NPL * SW ? tid + NTH * u : std::min(tid + NTH * u, NPL * SW - 1)));
+    __builtin_amdgcn_sched_barrier(0);   // issued here, not where the registers are wanted
+  };
+  auto commit = [&](int buf) FVAN_INLINE {
+    u32x4* w = reinterpret_cast<u32x4*>(&Ws[buf][0][0]);
+#pragma unroll
+    for (int u = 0; u < NPRE; ++u)
+      if (NTH * (u + 1) <= NPL * SW || tid + NTH * u < NPL * SW) w[tid + NTH * u] = pre[u];
+  };
   // the rows' values of a group of K chunks, loaded one group ahead
   float4 an[CG][LK / 4];
   auto load_a = [&](int grp) {
@@ -823,11 +811,11 @@ __global__ __launch_bounds__(512) void gemm_ln_bwd_kernel(const float* __restric
       for (int i = 0; i < LK / 4; ++i)
         an[cc][i] = *reinterpret_cast<const float4*>(A + ra * K + (grp * CG + cc) * KC + g * LK + 4 * i);
   };
-  FVAN_GL_FETCH(0);
+  fetch(0);
   load_a(0);
-  FVAN_GL_COMMIT(0);
+  commit(0);
   __syncthreads();
-  if (NG > 1) FVAN_GL_FETCH(1);
+  if (NG > 1) fetch(1);
   floatx4 acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -843,6 +831,7 @@ __global__ __launch_bounds__(512) void gemm_ln_bwd_kernel(const float* __restric
       for (int i = 0; i < LK / 4; ++i) cur[cc][i] = an[cc][i];
     if (grp + 1 < NG) load_a(grp + 1);
     else lr.load(X, resid, rbase, rows, g, c);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int cc = 0; cc < CG; ++cc) {
       FragA<MODE> fa;
@@ -859,32 +848,30 @@ __global__ __launch_bounds__(512) void gemm_ln_bwd_kernel(const float* __restric
       }
     }
     // the other stage was last read in group grp - 1, finished before the barrier that ended it
-    if (grp + 1 < NG) FVAN_GL_COMMIT((grp + 1) & 1);
+    if (grp + 1 < NG) commit((grp + 1) & 1);
     __syncthreads();                         // group grp + 1 is staged; stage grp & 1 is free
     // issued after the barrier, whose fence would otherwise wait for these loads
-    if (grp + 2 < NG) FVAN_GL_FETCH(grp + 2);
+    if (grp + 2 < NG) fetch(grp + 2);
   }
-#undef FVAN_GL_FETCH
-#undef FVAN_GL_COMMIT
   ln_bwd_rows<D>(acc, lr, ln_g, ln_b, rbase, rows, g, c, out, At, nullptr, ldT, red[wave]);
-  __syncthreads();
-  for (int k = tid; k < 2 * D; k += 64 * NW) {
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) sum += red[w][k];
-    part[(size_t)blockIdx.x * 2 * D + k] = sum;
-  }
+  store_col_part<D, NW>(red, part);
 }
 
 template <int MODE, int K, int NOUT, int EPI>
 inline hipError_t gemm_rows(const typename Mode<MODE>::ActT* A, int64_t rows, const void* pack, const EpiArgs& e,
-                            hipStream_t s) {
+                            hipStream_t s, bool few = false) {
   // the rows come either from A or, for K <= 128, from LayerNorm(e.ln_x)
   if (e.ln_x ? (K > 128) : (A == nullptr)) return hipErrorInvalidValue;
   if constexpr ((EPI == EPI_GELU || EPI == EPI_DGELU || EPI == EPI_STORE_KV) && K <= 128 && NOUT % 64 == 0) {
-    constexpr int R = 64 * StagedRowTiles<EPI>::value;
-    hipLaunchKernelGGL((gemm_rows_staged_kernel<MODE, K, NOUT, EPI>), dim3((int)((rows + R - 1) / R)), dim3(256), 0,
-                       s, A, rows, reinterpret_cast<const uint4*>(pack), e);
+    auto launch = [&](auto tiles, int col_blocks) {
+      constexpr int RT = decltype(tiles)::value, R = 64 * RT;
+      hipLaunchKernelGGL((gemm_rows_staged_kernel<MODE, K, NOUT, EPI, RT>), dim3((int)((rows + R - 1) / R), col_blocks),
+                         dim3(256), 0, s, A, rows, reinterpret_cast<const uint4*>(pack), e);
+    };
+    // few rows: also a workgroup per 64 output columns (one after the other, each waiting
+    // for its weights, is most of the time)
+    if (few) launch(std::integral_constant<int, 1>(), NOUT / 64);
+    else launch(std::integral_constant<int, StagedRowTiles<EPI>::value>(), 1);
   } else {
     hipLaunchKernelGGL((gemm_rows_kernel<MODE, K, NOUT, EPI>), dim3((int)((rows + kGemmRows - 1) / kGemmRows)),
                        dim3(256), 0, s, A, rows, reinterpret_cast<const uint4*>(pack), e);

@@ -261,3 +261,26 @@ def test_backward_at_the_edges_of_attention_and_row_tiles(n, window, prefix, bat
     m.log_prob_backward(s, torch.as_tensor(w, device="cuda"))
     torch.cuda.synchronize()
     assert _rel(to_np(m.grads).astype(np.float64), ref) <= GRAD_TOL[prec]
+
+
+@pytest.mark.parametrize("prec", [FP32, SPLIT])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_few_rows_and_many_rows_agree(d, prec):
+    """A pass over few rows takes row workgroups of half the size: ln q is the same bits on both sides of the rule
+    (a sample's values do not depend on the batch), at one row workgroup per CU and one sample more, and a gradient
+    that the added sample does not weigh in is the same up to the order of its sums (16k FP32 terms)."""
+    n, few = 16, 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    cfg = ModelConfig(n, d, 1, d // 16).with_mask(5, 3)
+    s = torch.as_tensor(random_spins(few + 1, n, 3), device="cuda")
+    w = torch.as_tensor(np.random.default_rng(4).standard_normal(few + 1).astype(np.float32), device="cuda")
+    w[few] = 0
+    out = []
+    for batch in (few, few + 1):
+        m, _ = make_model(cfg, batch, prec, seed=12)
+        m.grads.zero_()
+        lq = m.log_prob(s[:batch].contiguous())
+        m.log_prob_backward(s[:batch].contiguous(), w[:batch].contiguous())
+        torch.cuda.synchronize()
+        out.append((lq[:few].clone(), to_np(m.grads).astype(np.float64)))
+    assert torch.equal(out[0][0], out[1][0])
+    assert _rel(out[0][1], out[1][1]) <= 1e-4
