@@ -75,19 +75,6 @@ __device__ __forceinline__ floatx4 mma_dup_hl(const SplitDup& a, const SplitBf16
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l0, b8, acc, 0, 0, 0);
 }
 
-// Four consecutive rows of a feature-major output (dword-aligned: a sample's first row
-// need not be a multiple of four), rows past `live` left alone.
-typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ void store_rows4(float* __restrict__ dst, const floatx4& v, int live) {
-  if (live >= 4) {
-    *reinterpret_cast<float4u*>(dst) = float4u{v[0], v[1], v[2], v[3]};
-  } else {
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-      if (i < live) dst[i] = v[i];
-  }
-}
-
 constexpr float kMaxFloor = -1e30f;   // finite start of the running maximum (unscaled score units)
 constexpr int kKhStride = 20;         // K rows in LDS: 16 halves + 4 (40 bytes)
 constexpr int kVtStride = kKeyChunk + 8;   // V^T rows in LDS: one per dim
