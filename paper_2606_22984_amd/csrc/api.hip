@@ -80,9 +80,6 @@ static int check_config(const fvan_model_config* c) {
   if (c->precision != FVAN_FP32 && c->precision != FVAN_BF16_SPLIT)
     return fail(FVAN_EINVAL, "unknown precision (FVAN_FP32 = 0 or FVAN_BF16_SPLIT = 2)");
   if (c->workspaces & ~(FVAN_WS_SAMPLER | FVAN_WS_TEACHER)) return fail(FVAN_EINVAL, "unknown workspace bits");
-  // the decode kernel addresses a sample's keys and values of a layer with 32-bit byte offsets
-  if ((c->workspaces & FVAN_WS_SAMPLER) && (int64_t)2 * kv_geom(*c).S * c->d_model * kv_elem_bytes(c->precision) > INT32_MAX - 64)
-    return fail(FVAN_EUNSUPPORTED, "the keys and values of one sample and layer must fit 2 GiB");
   return FVAN_OK;
 }
 

@@ -1,6 +1,7 @@
 // Launch dispatch of the KV-cached decode kernel (decode_impl.h), and its
 // instantiations for single-spin models with 16-wide heads (the hot path);
-// decode_ext.hip instantiates the other head widths and the token models.
+// decode_ext.hip instantiates the other head widths and the token models,
+// decode_wide.hip every shape for caches past 32-bit offsets.
 #include "decode_impl.h"
 
 namespace fvan {
@@ -19,11 +20,15 @@ FVAN_DECODE_INST(32, 2, 16, false, 32)
 FVAN_DECODE_INST(64, 2, 16, false, 32)
 FVAN_DECODE_INST(128, 2, 16, false, 32)
 FVAN_DECODE_EXT_LIST(FVAN_DECODE_EXTERN)
+FVAN_DECODE_WIDE_LIST(FVAN_DECODE_WIDE_EXTERN)
 
 template <int D, int MODE, int DH>
 static hipError_t dispatch_tok(const DecodeShape& sh, const DecodeUnit& u0, const DecodeUnit* table, int n_units,
                                int total_tiles, int* queue, int grid, hipStream_t s) {
   if (sh.tile < 1 || sh.tile > 32) return hipErrorInvalidValue;
+  if (sh.wide)
+    return sh.tokens ? launch_d<D, MODE, DH, true, 32, true>(u0, table, n_units, total_tiles, queue, grid, s)
+                     : launch_d<D, MODE, DH, false, 32, true>(u0, table, n_units, total_tiles, queue, grid, s);
   if (sh.tile <= 16) {
     if constexpr (DH == 16)
       if (!sh.tokens) return launch_d<D, MODE, DH, false, 16>(u0, table, n_units, total_tiles, queue, grid, s);

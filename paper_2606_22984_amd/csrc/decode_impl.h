@@ -26,7 +26,7 @@
 // (sample_tile); 2D groups 45.1 -> 36.9 ms; same samples bit for bit.
 //
 // Template parameters: D = d_model, MODE = precision, DH = head width (16, 32
-// or 64), TOK = a model over 2^D-spin patch tokens: the head has `vocab`
+// or 64), WIDE = caches past 32-bit offsets (below), TOK = a model over 2^D-spin patch tokens: the head has `vocab`
 // outputs, the token is drawn from the V-way softmax by one uniform (walking
 // the vocabulary from the top, so V = 2 is the binary rule) and fed to the token
 // embedding of the next position; the token, not a spin, is written out.
@@ -83,6 +83,10 @@ __device__ __forceinline__ float reduce16(float v) { return row_sum16(v); }
 // no branch surrounds the access and the compiler knows how many loads are in flight
 // behind the one it waits for.  Loads are non-temporal, so that the stream does not
 // push the layer weights out of L2.
+// The block must fit 32-bit offsets (decode_wide).  The WIDE form of the kernel takes
+// a buffer per batch and plane from its 64-bit address instead, any length of cache; its
+// scalar registers are why it is not the only form (N=16 SK, 1024 samples: 150 against
+// 140 us; 2D L=16: 9.49 against 8.55 ms; a branch between the two: 166 us and 9.42 ms).
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t kv_rsrc_t;
 constexpr int kNoLane = 0x7FFFFFF0;          // past the end of any block
@@ -346,7 +350,7 @@ __device__ __forceinline__ float pick(const float (&v)[T], int i) {
   return x;
 }
 
-template <int D, int MODE, int DH, bool TOK, int KM>
+template <int D, int MODE, int DH, bool TOK, int KM, bool WIDE>
 __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& U, int local_tile) {
   typedef typename Mode<MODE>::KvT T;
   typedef DecodeSmem<D, MODE, TOK, KM> Sm;
@@ -450,13 +454,24 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
   // (zero) probabilities multiply zeros, not stale register contents
   auto issue = [&](Batch& x, int l, int m, int part, int nvis) FVAN_INLINE {
     const int lane = opaque(tid & 63), lrow = lane / LPR, lcol = (lane % LPR) * VEC;
-    const kv_rsrc_t r = kv_rsrc(kv_block(m, l), 2 * (int)(plane * sizeof(T)));
+    if constexpr (WIDE) {                   // a wave load is 64 x 16 consecutive bytes
+      const int s0 = part * UNR * RPL, bytes = min(max(nvis - s0, 0), UNR * RPL) * (D * (int)sizeof(T));
+      T* kb = kv_block(m, l) + (size_t)s0 * D;
+      const kv_rsrc_t rk = kv_rsrc(kb, bytes), rv = kv_rsrc(kb + plane, bytes);
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int s = (part * UNR + u) * RPL + lrow;
-      const int at = s < nvis ? (s * D + lcol) * (int)sizeof(T) : kNoLane;
-      x.k[u] = kv_load16(r, at, 0);
-      x.v[u] = kv_load16(r, at, (int)(plane * sizeof(T)));
+      for (int u = 0; u < UNR; ++u) {
+        x.k[u] = kv_load16(rk, 16 * lane + 1024 * u, 0);
+        x.v[u] = kv_load16(rv, 16 * lane + 1024 * u, 0);
+      }
+    } else {
+      const kv_rsrc_t r = kv_rsrc(kv_block(m, l), 2 * (int)(plane * sizeof(T)));
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const int s = (part * UNR + u) * RPL + lrow;
+        const int at = s < nvis ? (s * D + lcol) * (int)sizeof(T) : kNoLane;
+        x.k[u] = kv_load16(r, at, 0);
+        x.v[u] = kv_load16(r, at, (int)(plane * sizeof(T)));
+      }
     }
   };
   Batch ba, bb;
@@ -542,9 +557,17 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
             sum = 0.f;
             // append k_t (row group 0) and v_t (row group 1) to the cache: this wave
             // is the only reader of the sample's rows
-            kv_store16(kv_rsrc(kv_block(m, l), 2 * (int)(plane * sizeof(T))),
-                       *reinterpret_cast<const uint4*>(&sm.kv[m][lrow & 1][lcol]),
-                       lrow < 2 ? (int)((lrow * plane + slot * D + lcol) * sizeof(T)) : kNoLane);
+            if constexpr (WIDE) {            // one row each, from the lanes of the first row group
+              T* kb = kv_block(m, l) + (size_t)slot * D;
+              kv_store16(kv_rsrc(kb, D * (int)sizeof(T)), *reinterpret_cast<const uint4*>(&sm.kv[m][0][lcol]),
+                         16 * lane);
+              kv_store16(kv_rsrc(kb + plane, D * (int)sizeof(T)), *reinterpret_cast<const uint4*>(&sm.kv[m][1][lcol]),
+                         16 * lane);
+            } else {
+              kv_store16(kv_rsrc(kv_block(m, l), 2 * (int)(plane * sizeof(T))),
+                         *reinterpret_cast<const uint4*>(&sm.kv[m][lrow & 1][lcol]),
+                         lrow < 2 ? (int)((lrow * plane + slot * D + lcol) * sizeof(T)) : kNoLane);
+            }
           }
           const int s0 = part * RPL * UNR;
           if (slot >= s0 && slot < s0 + RPL * UNR) {   // the step's own row
@@ -880,7 +903,7 @@ __device__ void decode_tile(DecodeSmem<D, MODE, TOK, KM>& sm, const DecodeUnit& 
   __syncthreads();
 }
 
-template <int D, int MODE, int DH, bool TOK, int KM>
+template <int D, int MODE, int DH, bool TOK, int KM, bool WIDE>
 __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeUnit u0, const DecodeUnit* __restrict__ table,
                                                           int n_units, int total_tiles, int* queue) {
   __shared__ DecodeSmem<D, MODE, TOK, KM> sm;
@@ -903,17 +926,17 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeUnit u0, const D
         if (table[mid].tile0 <= tile) lo = mid; else hi = mid - 1;
       }
       const DecodeUnit U = table[lo];
-      decode_tile<D, MODE, DH, TOK, KM>(sm, U, tile - U.tile0);
+      decode_tile<D, MODE, DH, TOK, KM, WIDE>(sm, U, tile - U.tile0);
     } else {
-      decode_tile<D, MODE, DH, TOK, KM>(sm, u0, tile);
+      decode_tile<D, MODE, DH, TOK, KM, WIDE>(sm, u0, tile);
     }
   }
 }
 
-template <int D, int MODE, int DH, bool TOK, int KM>
+template <int D, int MODE, int DH, bool TOK, int KM, bool WIDE = false>
 hipError_t launch_d(const DecodeUnit& u0, const DecodeUnit* table, int n_units, int total_tiles, int* queue, int grid,
                     hipStream_t s) {
-  hipLaunchKernelGGL((decode_kernel<D, MODE, DH, TOK, KM>), dim3(grid), dim3(kThreads), 0, s, u0, table, n_units,
+  hipLaunchKernelGGL((decode_kernel<D, MODE, DH, TOK, KM, WIDE>), dim3(grid), dim3(kThreads), 0, s, u0, table, n_units,
                      total_tiles, queue);
   return hipGetLastError();
 }
@@ -936,5 +959,20 @@ hipError_t launch_d(const DecodeUnit& u0, const DecodeUnit* table, int n_units, 
   template hipError_t launch_d<D, MODE, DH, TOK, KM>(const DecodeUnit&, const DecodeUnit*, int, int, int*, int, \
                                                       hipStream_t);
 #define FVAN_DECODE_EXTERN(D, MODE, DH, TOK, KM) extern FVAN_DECODE_INST(D, MODE, DH, TOK, KM)
+
+// The WIDE instantiations (decode_wide.hip): every model shape, with 32-sample tiles.
+#define FVAN_DECODE_WIDE_LIST(X)                                                                                \
+  X(32, 0, 16) X(32, 2, 16) X(32, 0, 32) X(32, 2, 32) X(64, 0, 16) X(64, 2, 16) X(64, 0, 32) X(64, 2, 32)      \
+  X(64, 0, 64) X(64, 2, 64) X(128, 0, 16) X(128, 2, 16) X(128, 0, 32) X(128, 2, 32) X(128, 0, 64) X(128, 2, 64)
+#define FVAN_DECODE_WIDE_INST(D, MODE, DH)                                                                        \
+  template hipError_t launch_d<D, MODE, DH, false, 32, true>(const DecodeUnit&, const DecodeUnit*, int, int, int*, \
+                                                             int, hipStream_t);                                    \
+  template hipError_t launch_d<D, MODE, DH, true, 32, true>(const DecodeUnit&, const DecodeUnit*, int, int, int*,  \
+                                                            int, hipStream_t);
+#define FVAN_DECODE_WIDE_EXTERN(D, MODE, DH)                                                                      \
+  extern template hipError_t launch_d<D, MODE, DH, false, 32, true>(const DecodeUnit&, const DecodeUnit*, int, int, \
+                                                                    int*, int, hipStream_t);                       \
+  extern template hipError_t launch_d<D, MODE, DH, true, 32, true>(const DecodeUnit&, const DecodeUnit*, int, int,  \
+                                                                   int*, int, hipStream_t);
 
 }  // namespace fvan

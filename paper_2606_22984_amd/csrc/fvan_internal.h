@@ -110,9 +110,15 @@ struct DecodeShape {
   int d_model, precision, d_head;
   bool tokens;         // vocab-way head and token draw
   int tile;            // samples per workgroup: 4, 8, 16 or 32 (up to 16 on 16-row tiles where decode_has_tile16)
+  bool wide;           // decode_wide
 };
+// Whether the keys and values of one sample and layer are past the 32-bit offsets of the
+// ordinary decode kernels (c: with its window clamped to n_spins - 1).
+inline bool decode_wide(const fvan_model_config& c) {
+  return (int64_t)2 * kv_geom(c).S * c.d_model * kv_elem_bytes(c.precision) > INT32_MAX - 64;
+}
 inline DecodeShape decode_shape(const fvan_model_config& c, int tile = 32) {
-  return DecodeShape{c.d_model, c.precision, c.d_model / c.n_heads, c.vocab > 2, tile};
+  return DecodeShape{c.d_model, c.precision, c.d_model / c.n_heads, c.vocab > 2, tile, decode_wide(c)};
 }
 // Whether the decode kernel of this shape exists with 16-sample tiles.
 bool decode_has_tile16(const DecodeShape& sh);

@@ -383,6 +383,7 @@ int fvan_group_create(const fvan_group_unit* units, int32_t n_units, int32_t til
     DecodeUnit d = make_decode_unit(m, u.batch, u.seed, u.stream_id, u.spins, u.log_q, m->kv, tiles, 32);
     tiles += d.n_tiles;
     table.push_back(d);
+    g->shape.wide = g->shape.wide || decode_wide(m->cfg);
     g->kv_sample_max = std::max(g->kv_sample_max, m->kv_bytes / (size_t)m->cfg.max_batch);
     g->coup.push_back(*u.couplings);
     if (u.couplings->kind == FVAN_BONDS_DENSE || u.couplings->n_spins > 4096) g->ell_energy = false;

@@ -181,3 +181,17 @@ def test_binding_patch_geometry_equals_the_oracles():
         assert np.array_equal(fv.patch_sites(L, D), patch.patch_sites(L, D)), (L, D)
     with pytest.raises(ValueError):
         fv.patch_sites(5, 2)
+
+
+@pytest.mark.parametrize("n_layers", [0, 1])
+@pytest.mark.parametrize("window", [2 ** 21, 2 ** 31 - 1])
+def test_caches_past_32_bit_offsets_are_accepted(window, n_layers):
+    """The keys and values of one sample and layer may exceed 2 GiB (here 2^21 + 2 positions of d = 128 in FP32), and
+    full causal may be spelled with any window >= n_spins - 1: only the device can turn such a model down."""
+    c = fv.ModelConfigC(n_spins=2 ** 21 + 2, d_model=128, d_token=2, n_layers=n_layers, n_heads=8, vocab=2, window=window,
+                        prefix=0, max_batch=1, precision=0, workspaces=fv.WS_SAMPLER)
+    h = C.c_void_p()
+    rc = fv.lib().fvan_create_model(C.byref(c), C.byref(h))
+    assert rc in (0, -2, -3), fv.lib().fvan_last_error()
+    if rc == 0:
+        assert fv.lib().fvan_destroy_model(h) == 0

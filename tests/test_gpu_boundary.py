@@ -2,6 +2,8 @@
 time (no later call allocates device memory), a model created without a
 workspace refuses the calls that need it, and non-finite results are reported
 as FVAN_ENONFINITE by the next synchronising call."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -89,3 +91,15 @@ def test_nonfinite_parameters_are_reported():
     with pytest.raises(fv.FvanError, match="ENONFINITE"):
         m2.status()
     m2.status()
+
+
+def test_model_with_a_cache_past_32_bit_offsets():
+    """A sampler whose keys and values of one sample and layer exceed 2 GiB is created (any window >= n_spins - 1 is
+    full causal) and freed."""
+    for window in (2 ** 21 + 1, 2 ** 31 - 1):
+        c = fv.ModelConfigC(n_spins=2 ** 21 + 2, d_model=128, d_token=2, n_layers=1, n_heads=8, vocab=2, window=window,
+                            prefix=0, max_batch=1, precision=0, workspaces=fv.WS_SAMPLER)
+        h = C.c_void_p()
+        say("long cache, window", window)
+        assert fv.lib().fvan_create_model(C.byref(c), C.byref(h)) == 0, fv.lib().fvan_last_error()
+        assert fv.lib().fvan_destroy_model(h) == 0
