@@ -75,8 +75,20 @@ __global__ __launch_bounds__(kLmcThreads) void lmc_kernel(const int32_t* __restr
   }
 }
 
+typedef int int32x4 __attribute__((ext_vector_type(4)));
+typedef int int32x4u __attribute__((ext_vector_type(4), aligned(4)));   // at any entry of a table
+
+// Entry d of site s of a group's 4 DEG table entries, s = 0 .. 3 (selected, not indexed).
+template <int DEG>
+__device__ __forceinline__ int of_site(const int32x4 (&t)[DEG], int d, int s) {
+  const int e0 = t[d / 4][d % 4], e1 = t[(DEG + d) / 4][(DEG + d) % 4];
+  const int e2 = t[(2 * DEG + d) / 4][(2 * DEG + d) % 4], e3 = t[(3 * DEG + d) / 4][(3 * DEG + d) % 4];
+  const int lo = s & 1 ? e1 : e0, hi = s & 1 ? e3 : e2;
+  return s & 2 ? hi : lo;
+}
+
 // The same sweeps with one thread per group of four consecutive sites (the sites
-// that share a Philox counter), for degree <= DEG and at most 1024 groups: the
+// that share a Philox counter), for degree DEG <= 8 and at most 1024 groups: the
 // group's neighbours and bonds stay in registers for all sweeps and its four
 // uniforms are drawn once per sweep, where the kernel above reads the table again
 // each half-sweep and runs the generator for every site.  A thread holds its sites
@@ -84,14 +96,18 @@ __global__ __launch_bounds__(kLmcThreads) void lmc_kernel(const int32_t* __restr
 // handles two slots (the other two only in a wave where some group is not two and
 // two).  lpc threads per configuration (a power of two up to 256, or the whole
 // workgroup), blockDim.x / lpc configurations per workgroup.
+// The group's entries, 4 DEG in a row in each table, are read 16 bytes at a time and
+// given to the slots by selects.  Entry by entry the reads alone took longer than a
+// whole sweep of the kernel above, so that refinements of one or two sweeps were
+// slower: 16384 configurations of 1000 spins of degree 6, one sweep, 281 us there, 318
+// with reads by entry, 88 now; 3000 of 4096 spins 210, 460 and 83.
 // Bound by vector issue (the generator, the exponential and the byte reads of the
-// neighbours).  16384 configurations of 1000 spins, 10 sweeps: 2.43 -> 0.37 ms.
+// neighbours).  The 1000-spin case with 10 sweeps: 2.43 ms with the kernel above, 0.28 now.
 template <int DEG>
 __global__ __launch_bounds__(1024) void lmc_group_kernel(const int32_t* __restrict__ nbr, const float* __restrict__ J,
-                                                         const int8_t* __restrict__ colour, int n, int degree,
-                                                         int batch, int lpc, float beta, int sweeps, uint32_t k0,
-                                                         uint32_t k1, uint32_t tag, int8_t* __restrict__ spins,
-                                                         int32_t* __restrict__ accepted) {
+                                                         const int8_t* __restrict__ colour, int n, int batch, int lpc,
+                                                         float beta, int sweeps, uint32_t k0, uint32_t k1, uint32_t tag,
+                                                         int8_t* __restrict__ spins, int32_t* __restrict__ accepted) {
   extern __shared__ uint32_t lds[];          // per configuration: two copies of ngrp words
   __shared__ int count[64];
   const int ngrp = (n + 3) >> 2;
@@ -127,16 +143,36 @@ __global__ __launch_bounds__(1024) void lmc_group_kernel(const int32_t* __restri
     site[u] = o8 & 3;
     col[u] = (o8 >> 2) - 1;
   }
+  if (live && 4 * grp + 4 <= n) {
+    int32x4 t[DEG];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+    for (int i = 0; i < DEG; ++i) t[i] = reinterpret_cast<const int32x4u*>(nbr)[grp * DEG + i];
 #pragma unroll
-    for (int d = 0; d < DEG; ++d) {
-      const int64_t o = (int64_t)(4 * grp + site[u]) * degree + d;
-      const int j = live && col[u] >= 0 && d < degree ? nbr[o] : -1;
-      const bool ok = j >= 0 && j < n;
-      idx[u][d] = ok ? j : 0;
-      w[u][d] = ok ? J[o] : 0.f;
-    }
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int d = 0; d < DEG; ++d) idx[u][d] = of_site<DEG>(t, d, site[u]);
+#pragma unroll
+    for (int i = 0; i < DEG; ++i) t[i] = reinterpret_cast<const int32x4u*>(J)[grp * DEG + i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int d = 0; d < DEG; ++d) {
+        const bool ok = idx[u][d] >= 0 && idx[u][d] < n;
+        w[u][d] = ok ? __int_as_float(of_site<DEG>(t, d, site[u])) : 0.f;
+        idx[u][d] = ok ? idx[u][d] : 0;
+      }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int d = 0; d < DEG; ++d) {
+        const int64_t o = (int64_t)(4 * grp + site[u]) * DEG + d;
+        const int j = live && col[u] >= 0 ? nbr[o] : -1;
+        const bool ok = j >= 0 && j < n;
+        idx[u][d] = ok ? j : 0;
+        w[u][d] = ok ? J[o] : 0.f;
+      }
+  }
   const bool more0 = __any(col[2] == 0 || col[3] == 0), more1 = __any(col[0] == 1 || col[1] == 1);
   __syncthreads();
   int p = 0, acc = 0;
@@ -201,9 +237,11 @@ hipError_t launch_lmc(int32_t n, int32_t degree, const int32_t* nbr, const float
     const int threads = std::max(lpc, 256), ncfg = threads / lpc;
     const dim3 grid((batch + ncfg - 1) / ncfg), block(threads);
     const size_t bytes = (size_t)ncfg * 2 * ngrp * 4;
-    auto kern = degree <= 4 ? lmc_group_kernel<4> : degree <= 6 ? lmc_group_kernel<6> : lmc_group_kernel<8>;
-    hipLaunchKernelGGL(kern, grid, block, bytes, s, nbr, J, colour, n, degree, batch, lpc, (float)beta, sweeps, k0, k1,
-                       stream_tag, spins, accepted);
+    decltype(&lmc_group_kernel<1>) kernels[8] = {lmc_group_kernel<1>, lmc_group_kernel<2>, lmc_group_kernel<3>,
+                                                 lmc_group_kernel<4>, lmc_group_kernel<5>, lmc_group_kernel<6>,
+                                                 lmc_group_kernel<7>, lmc_group_kernel<8>};
+    hipLaunchKernelGGL(kernels[degree - 1], grid, block, bytes, s, nbr, J, colour, n, batch, lpc, (float)beta, sweeps,
+                       k0, k1, stream_tag, spins, accepted);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(lmc_kernel, dim3(batch), dim3(kLmcThreads), 0, s, nbr, J, colour, n, degree, (float)beta, sweeps,

@@ -146,3 +146,30 @@ def test_lmc_any_graph_and_colouring(n, degree, batch):
             continue
         assert np.array_equal(got[b], ref[0]) and gacc[b] == racc[0], f"configuration {b}"
     assert excused <= max(1, batch // 8)
+
+
+@pytest.mark.parametrize("degree", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("n,offset", [(3, 0), (66, 1), (1023, 2), (2052, 3)])
+def test_lmc_tables_at_any_alignment(n, offset, degree):
+    """One sweep at every degree of the register kernel, with tables that start `offset` entries into their
+    allocations (the kernel reads them 16 bytes at a time) and a last group of two, three or four sites."""
+    rng = np.random.default_rng(10 * n + degree)
+    nbr = rng.integers(-1, n, (n, degree)).astype(np.int32)
+    J = rng.standard_normal((n, degree)).astype(np.float32)
+    col = (np.arange(n) % 2).astype(np.int8)
+    spins = random_spins(3, n, 4)
+    tn = torch.full((n * degree + offset,), -1, dtype=torch.int32, device="cuda")
+    tj = torch.zeros(n * degree + offset, device="cuda")
+    tn[offset:] = torch.as_tensor(nbr.reshape(-1), device="cuda")
+    tj[offset:] = torch.as_tensor(J.reshape(-1), device="cuda")
+    tc = torch.as_tensor(col, device="cuda")
+    g = fv.LmcGraph(n, tn, tj, tc, fv.LmcC(degree=degree, nbr=tn.data_ptr() + 4 * offset, J=tj.data_ptr() + 4 * offset,
+                                           colour=tc.data_ptr(), sweeps=1))
+    t = torch.as_tensor(spins, device="cuda")
+    fv.lmc_refine(g, t, 0.7, 5, 17)
+    torch.cuda.synchronize()
+    got = to_np(t)
+    adj = [[(int(j), float(w)) for j, w in zip(nbr[i], J[i]) if j >= 0] for i in range(n)]
+    for b in range(3):
+        ref, _, marg = refine.metropolis_checkerboard(spins[b:b + 1], adj, col, 0.7, 1, 5, 17, b0=b, margins=True)
+        assert marg[0] < TIE or np.array_equal(got[b], ref[0]), f"configuration {b}"
