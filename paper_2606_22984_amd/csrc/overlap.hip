@@ -25,7 +25,8 @@
 namespace fvan {
 
 constexpr int kOvMaxSpins = 16000;
-constexpr int kOvHistBytes = 65536;      // LDS of the histogram copies
+constexpr int kOvHistBytes = 65536;      // LDS of the histogram copies, 256 x 256 blocks
+constexpr int kOvHistSmall = 8192;       // and smaller blocks
 constexpr int kOvPitch = 80;             // bytes per staged row: 64 spins + padding (conflict-free 16-byte reads)
 
 typedef int int4v __attribute__((ext_vector_type(4)));
@@ -147,22 +148,35 @@ __global__ void zero_u64_kernel(unsigned long long* p, int n) {
 hipError_t launch_overlap(int32_t batch, int32_t n, const int8_t* spins, unsigned long long* counts, hipStream_t s) {
   if (batch < 1 || n < 1 || n > kOvMaxSpins) return hipErrorInvalidValue;
   hipLaunchKernelGGL(zero_u64_kernel, dim3((n + 256) / 256), dim3(256), 0, s, counts, n + 1);
-  int copies = 16;
-  while (copies > 1 && (size_t)(n + 2) * copies * 4 > kOvHistBytes) copies /= 2;
-  const size_t lds = (size_t)(n + 2) * copies * 4;
-  auto pairs = [&](int bt) {
+  const auto pairs = [&](int bt) {
     const int64_t b = (batch + bt - 1) / bt;
     return b * (b + 1) / 2;
   };
-  // the largest blocks (fewest reads per product) that still give every compute
-  // unit a block pair or more
-  if (pairs(256) >= 512)
-    hipLaunchKernelGGL((overlap_kernel<256, 4, 2>), dim3(256), dim3(512), lds, s, spins, batch, n, copies, counts);
-  else if (pairs(128) >= 512)
-    hipLaunchKernelGGL((overlap_kernel<128, 2, 2>), dim3(512), dim3(256), lds, s, spins, batch, n, copies, counts);
+  // as many histogram copies as fit `bytes`
+  const auto launch = [&](auto kern, int threads, int64_t grid, size_t bytes) {
+    int copies = 16;
+    while (copies > 1 && (size_t)(n + 2) * copies * 4 > bytes) copies /= 2;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), (size_t)(n + 2) * copies * 4, s, spins, batch, n,
+                       copies, counts);
+  };
+  // Block size by the rounds of workgroups over 256 compute units.  A block pair of 64
+  // costs the most reads per product but the least on a chip that it does not fill: up
+  // to one per unit, or two while their histograms leave room for two (1800 samples of
+  // 12000 spins: 111 us, with 128 153; of 16000, where one fits: 229 with 64, 166 with
+  // 128).  Two workgroups of 128 share a unit, and a round of theirs takes 2/3 of a round
+  // of one of 256 (5000 samples of 1000 spins, 2 against 1 rounds: 45 and 34 us; 3000, 1
+  // and 1: 24 and 31; 6000, 3 and 2: 62 and 60, and of 64 spins 17 and 19).
+  // The smaller blocks get 8 KB of histogram copies: with 64 KB one workgroup had a unit
+  // to itself (2000 samples of 1000 spins: 42 us with 64 and 64 KB, 25 with 64 and 8 KB, 20
+  // with 128; the kernel before the staged blocks took 29).
+  const int64_t p64 = pairs(64), p128 = pairs(128), p256 = pairs(256);
+  const int64_t r128 = (p128 + 511) / 512, r256 = (p256 + 255) / 256;
+  if (p64 <= 256 || (p64 <= 450 && n <= 14000))
+    launch(overlap_kernel<64, 2, 2>, 256, p64, kOvHistSmall);
+  else if (2 * r128 <= 3 * r256)
+    launch(overlap_kernel<128, 2, 2>, 256, std::min<int64_t>(p128, 512), kOvHistSmall);
   else
-    hipLaunchKernelGGL((overlap_kernel<64, 2, 2>), dim3((unsigned)std::min<int64_t>(pairs(64), 1024)), dim3(256), lds, s,
-                       spins, batch, n, copies, counts);
+    launch(overlap_kernel<256, 4, 2>, 512, std::min<int64_t>(p256, 256), kOvHistBytes);
   return hipGetLastError();
 }
 

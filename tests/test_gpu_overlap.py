@@ -65,3 +65,21 @@ def test_overlap_histogram_block_edges(B, N, start):
         upper = np.arange(B)[None, :] > np.arange(a, min(a + 1024, B))[:, None]
         ref += np.bincount(k[upper], minlength=N + 1)
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("B,N", [(1408, 66), (1409, 66), (1856, 130), (1857, 130), (1500, 14001), (3968, 300), (6000, 64),
+                                 (6000, 65), (7100, 64)])
+def test_overlap_histogram_where_the_block_size_changes(B, N):
+    """Exact counts on both sides of the rule's lines between blocks of 64, 128 and 256 samples (one and two block
+    pairs of 64 per compute unit, one to three rounds of the larger ones, histograms too large for two)."""
+    g = torch.Generator(device="cuda").manual_seed(B + N)
+    s = torch.randint(0, 2, (B, N), generator=g, device="cuda", dtype=torch.int8) * 2 - 1
+    say(f"overlap B={B} N={N}")
+    got = to_np(fv.overlap_histogram(s))
+    f = to_np(s).astype(np.float32)
+    ref = np.zeros(N + 1, dtype=np.int64)
+    for a in range(0, B, 1024):                    # integers below 2^24: exact in float32
+        k = ((f[a:a + 1024] @ f.T + N) / 2).astype(np.int64)
+        upper = np.arange(B)[None, :] > np.arange(a, min(a + 1024, B))[:, None]
+        ref += np.bincount(k[upper], minlength=N + 1)
+    assert np.array_equal(got, ref)
