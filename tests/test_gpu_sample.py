@@ -282,3 +282,22 @@ def test_token_head_of_any_vocabulary(vocab, batch):
     assert int(tok.max()) < vocab
     ref = to_np(m.log_prob_tokens(tok)).astype(np.float64)
     assert np.max(np.abs(to_np(lq).astype(np.float64) - ref)) / cfg.n_spins <= 5e-5
+
+
+@pytest.mark.parametrize("n,batch,offset", [(1, 3, 0), (12, 17, 0), (13, 17, 1), (63, 33, 0), (64, 16, 0), (65, 17, 1),
+                                            (128, 4096, 0), (129, 4097, 0), (256, 4095, 1), (257, 100, 0), (511, 31, 0),
+                                            (512, 33, 0), (513, 20, 0), (4096, 33, 0)])
+def test_energy_dense_of_unit_couplings_is_exact(n, batch, offset):
+    """Couplings of +-1 (n^2 <= 2^24 of them): every partial sum is an integer that FP32 holds, in any order, so the
+    energies are equal to the integer ones; an element lost, doubled or taken from another row would show."""
+    rng = np.random.default_rng(n + 1)
+    up = np.triu(rng.choice(np.array([-1, 1], np.int8), (n, n)), 1)
+    J = up + up.T
+    store = torch.zeros(n * n + offset, device="cuda")
+    store[offset:] = torch.as_tensor(J.reshape(-1).astype(np.float32), device="cuda")
+    c = fv.CouplingsC(n_spins=n, kind=fv.BONDS_DENSE, degree=0, nbr=None, J=store.data_ptr() + 4 * offset)
+    coup = fv.Couplings(n, fv.BONDS_DENSE, 0, None, store, c)
+    s = random_spins(batch, n, 3)
+    E = to_np(fv.energy(coup, torch.as_tensor(s, device="cuda"))).astype(np.float64)
+    x = s.astype(np.float64)
+    assert np.array_equal(E, -0.5 * ((x @ J.astype(np.float64)) * x).sum(1))
