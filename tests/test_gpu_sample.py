@@ -301,3 +301,18 @@ def test_energy_dense_of_unit_couplings_is_exact(n, batch, offset):
     E = to_np(fv.energy(coup, torch.as_tensor(s, device="cuda"))).astype(np.float64)
     x = s.astype(np.float64)
     assert np.array_equal(E, -0.5 * ((x @ J.astype(np.float64)) * x).sum(1))
+
+
+@pytest.mark.parametrize("prec", ALL_PRECISIONS)
+@pytest.mark.parametrize("d,dh,vocab", [(32, 16, 2), (64, 16, 2), (128, 16, 2), (64, 32, 2), (128, 64, 256)])
+def test_samples_of_every_batch_are_those_of_the_largest(d, dh, vocab, prec):
+    """Sample b is the same bits in every batch, against the largest (two rounds of 32-sample workgroups): one sample,
+    a single ragged 4-sample workgroup, and every workgroup size with a ragged last one."""
+    cfg = ModelConfig(45, d, 2, d // dh, d_token=2 if vocab == 2 else 8, vocab=vocab, window=20, prefix=16)
+    m = fv.Model(cfg, 8200, prec, init_params(cfg, 3, "random"), workspaces=fv.WS_SAMPLER)
+    call = m.sample if vocab == 2 else m.sample_tokens
+    ref_s, ref_lq = call(8200, 11, 2)
+    assert torch.isfinite(ref_lq).all() and len(torch.unique(ref_s)) > 1
+    for B in (1, 3, 37, 1029, 2051, 4099):
+        s, lq = call(B, 11, 2)
+        assert torch.equal(s, ref_s[:B]) and torch.equal(lq, ref_lq[:B]), B
