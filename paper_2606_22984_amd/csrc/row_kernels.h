@@ -257,7 +257,13 @@ __global__ __launch_bounds__(256) void gemm_rows_staged_kernel(const typename Mo
   const bool full = r0 + R <= rows;
   OT* out = reinterpret_cast<OT*>(e.out);
   AT* outT = reinterpret_cast<AT*>(e.outT);
-  for (int ng = blockIdx.y; ng < NG; ng += gridDim.y) {
+  // The column groups of this workgroup: all of them, or with few rows one each.  In split
+  // mode at d = 64 the first group and the stride have to be known to the compiler: read at
+  // run time they took it to 132 registers, three workgroups a compute unit instead of four
+  // (1M rows: 168 -> 176 us).  Elsewhere the run-time form is the faster one (FP32, d = 64:
+  // 325 against 340 us).
+  constexpr bool ALL = Mode<MODE>::SPLIT && K <= 64 && RT > 1;   // launched with gridDim.y = 1
+  for (int ng = ALL ? 0 : (int)blockIdx.y; ng < NG; ng += ALL ? 1 : (int)gridDim.y) {
     if constexpr (EPI == EPI_DGELU) {
       // stage the pre-activation tile (256-byte row segments)
 #pragma unroll
