@@ -618,9 +618,12 @@ __device__ __forceinline__ void store_col_part(const float (*red)[2 * D], float*
 // used to wait for every store before it.  The rows of x and dY for the LayerNorm
 // backward are loaded during the last chunk.  1M rows, d = 128, split: 2.30 -> 2.10 ms
 // (4.9 GB written and 2.1 GB read: 1.4 ms at the rate of a copy).
+// FP32 up to d = 64 is held to the 128 registers that let two workgroups share a compute
+// unit: at d = 64 it would take one more (1M rows: 1.32 ms before the rows' early loads,
+// 1.40 with them at 129 registers, 1.31 at 128).
 // p1: W1 [4D x D] pack; p2t: W2^T [4D x D] pack; p1t: W1^T [D x 4D] pack.
 template <int MODE, int D, int NW = 8>
-__global__ __launch_bounds__(64 * NW) void ffn_bwd_fused_kernel(
+__global__ __launch_bounds__(64 * NW, !Mode<MODE>::SPLIT && D <= 64 && NW == 8 ? 4 : 1) void ffn_bwd_fused_kernel(
     const float* __restrict__ X, const float* __restrict__ dY, const float* __restrict__ ln_g,
     const float* __restrict__ ln_b, int64_t rows, const uint4* __restrict__ p1, const uint4* __restrict__ p2t,
     const uint4* __restrict__ p1t, const float* __restrict__ b1, typename Mode<MODE>::ActT* __restrict__ Gt,

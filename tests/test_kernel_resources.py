@@ -57,6 +57,9 @@ def _template(name, *args):
     # QKV projection of many rows, d = 64: four workgroups of four waves a compute unit
     ("gemm_rows_staged_kernel", (0, 64, 192, 0, 2), 4),
     ("gemm_rows_staged_kernel", (2, 64, 192, 0, 2), 4),
+    # feed-forward backward of many rows, FP32: two workgroups of eight waves
+    ("ffn_bwd_fused_kernel", (0, 32, 8), 4),
+    ("ffn_bwd_fused_kernel", (0, 64, 8), 4),
 ])
 def test_waves_per_simd(kernels, name, args, waves):
     found = [k for n, k in kernels.items() if n.startswith(_template(name, *args))]
