@@ -406,7 +406,7 @@ static __global__ __launch_bounds__(kDkvThreads) void attn_bwd_dkv_f16(const _Fl
   float sraw = 0.f;
   // the pointers walk from block to block: formed anew, their 64-bit products were an
   // eighth of the kernel's vector instruction time.  With the four-row stores at the
-  // end (16 lines an instruction before, at a dword each): 1.79 -> 1.54 ms (1024 samples
+  // end (16 lines an instruction before, at a dword each): 1.79 -> 1.54 ms alone (1024 samples
   // of 1000 spins, 8 heads, 226 visible keys), 0.66 -> 0.47 ms (34 visible keys)
   const float* gp = dO + (rowbase + j0 + gr) * D + h * 16 + gc;
   const _Float16* qp = QKV + (rowbase + j0 + qr) * 3 * D + h * 16 + qc;

@@ -111,10 +111,12 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const float* __restrict__
 
 // out[k] += sum_{i < n} part[i * width + k] in a fixed order: kColSlices slices of
 // consecutive partials, each summed by four interleaved threads, then the slices in
-// order.  Both levels keep several loads in flight (the adds stay in order): one at a
-// time, the sums of 8192 partials took 36 + 37 us beside the weight gradients, now
-// 5 + 5 us.  Up to 8 partials per slice, one launch does both levels (the slice
-// sums meet in LDS).
+// order.  Both levels keep several loads in flight (the adds stay in order).  8192
+// partials, one load at a time and now: alone 15 + 5 -> 5.5 + 4.5 us, beside the weight
+// gradients (256-spin samples) 38 + 18 -> 5 + 7 us.  What they cost a call is more than
+// that: the second launch can wait for the weight gradients to leave it a slot (220 us
+// before and after in the gradient of 1024 samples of 1000 spins, d = 128).  Up to 8
+// partials per slice, one launch does both levels (the slice sums meet in LDS).
 constexpr int kColSlices = 64;
 template <int U, typename F>
 __device__ __forceinline__ float ordered_sum(int i0, int i1, int step, F&& load) {

@@ -219,9 +219,11 @@ int device_cus(int dev) {
 // a batch that leaves compute units idle is spread over them.  Below four samples
 // nothing more is gained: each of the four SIMDs then has one sample.  Measured
 // against 16-sample workgroups: N=16 SK, 1024 samples 198 -> 141 us (4 per
-// workgroup); patched 3D step, 2048 samples 16.0 -> 15.0 ms (8).  And against 16
-// where 32 fit (two rounds of workgroups instead of one): d = 64, N = 64, 6000
-// samples 1.4 to 1.5 times faster.
+// workgroup); patched 3D step, 2048 samples 16.0 -> 15.0 ms (8).  And 32 where 16
+// would take two rounds of workgroups, 5000 samples of 100 spins against the kernel
+// that took 16: d = 32 5.59 -> 4.34 ms (FP32) and 4.26 -> 3.04 (split), d = 64 10.9 -> 8.5
+// and 6.96 -> 4.78, d = 128 23.9 -> 18.6 and 14.5 -> 9.5, of 256 tokens 27.8 -> 20.5 and
+// 18.5 -> 12.0 (7 to 20% of a call is the loads issued ahead, as at 9000 samples).
 int sample_tile(const fvan_model* m, int32_t batch) {
   const int cus = device_cus(m->device);
   for (int tile = 4; tile < 32; tile *= 2)

@@ -23,7 +23,8 @@
 //             workgroup per 64 columns (muon_begin / scale / gram / update
 //             kernels).  One workgroup per matrix waited on L2 for its Gram
 //             operands: 1.78 ms for two layers' matrices, 0.21 ms now
-// Every form sums in the same order.
+// Every form adds the products in the same order.  The norm of the momentum, in FP64, is
+// one workgroup's sum up to m = 64 and 32 workgroups' sums at m = 128.
 // The standalone orthogonalisation (no workspace) is one workgroup with Z in
 // global memory.
 #include <cmath>

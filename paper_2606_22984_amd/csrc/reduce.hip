@@ -1,8 +1,8 @@
 // Batch reductions in FP64 on the device: the free-energy estimator (Eq. 5),
 // its sample variance, the REINFORCE baseline and weights (Eq. 19), the mean
-// energy and the gradient norm.  Each runs in ONE workgroup with a fixed
-// per-thread stride and a fixed reduction tree, so results are bitwise
-// reproducible run to run.
+// energy and the gradient norm.  Each runs in one workgroup (the gradient norm of
+// more than 65536 parameters in 64, then one) with a fixed per-thread stride and a
+// fixed reduction tree, so results are bitwise reproducible run to run.
 #include "device_common.h"
 #include "fvan_internal.h"
 

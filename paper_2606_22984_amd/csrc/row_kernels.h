@@ -214,7 +214,10 @@ template <int EPI> struct StagedRowTiles { static constexpr int value = EPI == E
 // idle while two waves share a SIMD's matrix core.  Gradient of two layers with 128 and
 // with 64 rows: 371 -> 316 us at 4096 rows, 445 -> 388 at 16384 (d = 64, FP32), 1148 -> 872
 // (d = 128, FP32), 605 -> 589 (d = 128, split); past one workgroup per CU, at 17600 rows,
-// 626 -> 720 (d = 128, split) and 459 -> 463 (d = 64, FP32).
+// 626 -> 720 (d = 128, split) and 459 -> 463 (d = 64, FP32).  With the other changes of the
+// row kernels, against the kernels without them, at 16000 and 17600 rows: d = 32 287 -> 260
+// and 304 -> 286 (FP32), 294 -> 272 and 303 -> 285 (split), d = 64 split 379 -> 339 and
+// 388 -> 362.
 inline bool few_rows(int64_t rows, int cus) { return (rows + 63) / 64 <= std::min(cus, 1024); }
 
 template <int MODE, int K, int NOUT, int EPI, int RT>
@@ -616,8 +619,8 @@ __device__ __forceinline__ void store_col_part(const float (*red)[2 * D], float*
 // overlapped with them.  The loop holds no load that is used at once and no branch
 // around a store: memory counts complete in order, and the biases' load of each tile
 // used to wait for every store before it.  The rows of x and dY for the LayerNorm
-// backward are loaded during the last chunk.  1M rows, d = 128, split: 2.30 -> 2.10 ms
-// (4.9 GB written and 2.1 GB read: 1.4 ms at the rate of a copy).
+// backward are loaded during the last chunk.  1.02M rows, d = 128, split, alone: 2.30 ->
+// 2.10 ms (11 D floats written a row and 4 D read, 7.9 GB: 1.6 ms at the rate of a copy).
 // FP32 up to d = 64 is held to the 128 registers that let two workgroups share a compute
 // unit: at d = 64 it would take one more (1M rows: 1.32 ms before the rows' early loads,
 // 1.40 with them at 129 registers, 1.31 at 128).
@@ -765,7 +768,8 @@ __global__ __launch_bounds__(64 * NW, !Mode<MODE>::SPLIT && D <= 64 && NW == 8 ?
 // all waves, CG K-chunks at a time, in two alternating buffers (one barrier per
 // group), the group after next fetched into registers meanwhile.  Bound by HBM: each
 // wave reads its own rows of dQKV, loaded one group ahead, and x and resid, loaded
-// during the last group (1M rows, d = 128, split: 0.86 -> 0.76 ms, 3.7 GB, 4.8 TB/s).
+// during the last group (1.02M rows, d = 128, split, alone: 0.86 -> 0.76 ms, 3.7 GB,
+// 4.8 TB/s).
 template <int MODE, int D, int K, int NW = 8>
 __global__ __launch_bounds__(64 * NW) void gemm_ln_bwd_kernel(const float* __restrict__ A, int64_t rows,
                                                           const uint4* __restrict__ pack, const float* __restrict__ X,
