@@ -111,21 +111,24 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const float* __restrict__
 
 // out[k] += sum_{i < n} part[i * width + k] in a fixed order: kColSlices slices of
 // consecutive partials, each summed by four interleaved threads, then the slices in
-// order.  Both levels keep several loads in flight (the adds stay in order).  8192
-// partials, one load at a time and now: alone 15 + 5 -> 5.5 + 4.5 us, beside the weight
-// gradients (256-spin samples) 38 + 18 -> 5 + 7 us.  What they cost a call is more than
-// that: the second launch can wait for the weight gradients to leave it a slot (220 us
-// before and after in the gradient of 1024 samples of 1000 spins, d = 128).  Up to 8
-// partials per slice, one launch does both levels (the slice sums meet in LDS).
+// order.  Both levels keep several loads in flight (the adds stay in order), within 32
+// registers: two workgroups of the W2 gradient (split mode, d = 128), which runs beside
+// them, leave a SIMD no more.  8192 partials beside the weight gradients: 35 + 17 us with
+// one load at a time, 9 + 195 with 32 loads and 66 registers in the second launch, which
+// then waited for a workgroup of the gradient to end, 9 + 12 now (alone 15 + 5 at first,
+// 5.5 + 4.5 now).  Up to 8 partials per slice, one launch does both levels (the slice sums
+// meet in LDS).
 constexpr int kColSlices = 64;
 template <int U, typename F>
 __device__ __forceinline__ float ordered_sum(int i0, int i1, int step, F&& load) {
   float s = 0.f;
   int i = i0;
+#pragma unroll 1
   for (; i + (U - 1) * step < i1; i += U * step) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = load(i + u * step);
+    __builtin_amdgcn_sched_barrier(0);   // the loads of a round in flight together
 #pragma unroll
     for (int u = 0; u < U; ++u) s += v[u];
   }
@@ -133,16 +136,22 @@ __device__ __forceinline__ float ordered_sum(int i0, int i1, int step, F&& load)
   return s;
 }
 
+// p[i], i < 2^30: p is the same for the wave, so that a load takes one register of address
+// for all of a round instead of two each
+__device__ __forceinline__ float at32(const float* __restrict__ p, uint32_t i) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + (uint32_t)(4u * i));
+}
+
 __global__ __launch_bounds__(256) void colsum_slices_kernel(const float* __restrict__ part, int n, int width,
                                                             float* __restrict__ part2) {
   __shared__ float red[4][64];
   const int k = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int sub = threadIdx.x >> 6;
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int slice = blockIdx.y;
   const int per = (n + kColSlices - 1) / kColSlices;
   const int i0 = slice * per, i1 = min(n, i0 + per);
-  const float* p = part + min(k, width - 1);
-  red[sub][threadIdx.x & 63] = ordered_sum<8>(i0 + sub, i1, 4, [&](int i) { return p[(size_t)i * width]; });
+  const uint32_t kc = min(k, width - 1);
+  red[sub][threadIdx.x & 63] = ordered_sum<8>(i0 + sub, i1, 4, [&](int i) { return at32(part + (size_t)i * width, kc); });
   __syncthreads();
   if (sub == 0 && k < width)
     part2[(size_t)slice * width + k] = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
@@ -150,7 +159,7 @@ __global__ __launch_bounds__(256) void colsum_slices_kernel(const float* __restr
 
 __global__ void colsum_final_kernel(const float* __restrict__ part2, int width, float* __restrict__ out) {
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < width; k += gridDim.x * blockDim.x)
-    out[k] += ordered_sum<32>(0, kColSlices, 1, [&](int i) { return part2[(size_t)i * width + k]; });
+    out[k] += ordered_sum<16>(0, kColSlices, 1, [&](int i) { return at32(part2 + (size_t)i * width, k); });
 }
 
 // Both levels for n <= 8 kColSlices: 16 columns per workgroup, thread (slice group, column).

@@ -67,3 +67,13 @@ def test_waves_per_simd(kernels, name, args, waves):
     vgprs = found[0][".vgpr_count"]
     assert 512 // ((vgprs + 7) // 8 * 8) >= waves, f"{vgprs} VGPRs"
     assert found[0][".vgpr_spill_count"] == 0
+
+
+@pytest.mark.parametrize("name", ["colsum_slices_kernel", "colsum_final_kernel"])
+def test_column_sums_fit_beside_the_weight_gradients(kernels, name):
+    """The LayerNorm column sums run on the caller's stream while the side stream fills the chip with the W2 gradient
+    (two 8-wave workgroups a compute unit): they need no more registers than these leave, or wait for one to end."""
+    wgrad, = (k for n, k in kernels.items() if n.startswith(_template("wgrad_kernel", 2, 128, 176)))
+    kernel, = (k for n, k in kernels.items() if n.startswith(f"_ZN4fvan{len(name)}{name}E"))
+    rounded = [(k[".vgpr_count"] + 7) // 8 * 8 for k in (wgrad, kernel)]
+    assert rounded[1] <= 512 - 4 * rounded[0]
